@@ -232,7 +232,9 @@ caee_status_t caee_moe_layer(const caee_layer_desc_t* desc, const void* x,
  * needs nothing in the array cleared: every byte the kernels read is written
  * earlier in the same call.
  * Returns CAEE_ERR_UNSUPPORTED, launching nothing, when the call needs more
- * than CAEE_SCRATCH_BYTES (caee_workspace_size tells).  Every call on one GPU
+ * than CAEE_SCRATCH_BYTES (caee_workspace_size tells; the transposed block
+ * scales of FP8 batches of 33 to 256 tokens, at most 1/64 of the rest, do not
+ * count).  Every call on one GPU
  * uses the same array: calls that overlap on one GPU (different streams or
  * threads without ordering between them) race and give undefined results. */
 caee_status_t caee_moe_layer_noalloc(const caee_layer_desc_t* desc, const void* x,

@@ -312,42 +312,54 @@ caee_status_t ffn_begin(const caee_layer_desc_t* d, const FfnParams& p, const Ws
 }
 
 caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, FfnCall* call,
-                         bool big_on_side) {
+                         bool two_streams) {
     const int nb_small = small_token_blocks(*d), nb_big = call_big_blocks(*d, p.tiled);
+    const bool all_big = call_chunk_small(*d, p.tiled) == 0;   // then the small list is empty
     hipStream_t s = call->main;
-    // The big chunks (few, long, latency-bound work items) run on a side
-    // stream next to the small ones (many, bandwidth-bound): disjoint rows.
-    // The fork comes after routing, which built their list.
-    hipStream_t sb = s;
-    if (nb_big && big_on_side && kBigConcurrent) {
+    // The 8-bit prefill kernel reads its rows' block scales transposed and in
+    // permuted row order: gathered here for x (before the fork, so that the
+    // big chunks' gate/up is the first of the two to find the CUs free),
+    // written so by its own gate/up for H.
+    const bool gemm8 = nb_big && d->w_dtype == CAEE_FP8_E4M3 && gemm_fp8_applies(*d, p.tiled);
+    if (gemm8) {
+        FfnParams pb = p;
+        pb.list = 1;
+        CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, s, "gather x scales",
+                              [&] { return launch_gather_xs(pb, L.max_chunks, s); }));
+    }
+    // The small chunks (many, bandwidth-bound) run on a side stream next to
+    // the big ones (few, long work items): disjoint rows.  The fork comes
+    // after routing, which built their lists, and the side stream starts some
+    // 6 us later, so the big items, each of which needs a whole CU, are placed
+    // first; behind the small ones they waited for those to drain (R1-shaped
+    // layer: 8-bit T = 200 1939 -> 1886 us, skewed 727 -> 704; bf16 skewed
+    // T = 300 1543 -> 1469, others within 1 %).
+    hipStream_t s_small = s;
+    if (nb_big && !all_big && two_streams && kBigConcurrent) {
         SideStream* ss = nullptr;
         CAEE_TRY(side_stream(&ss));
         call->side = ss->stream;
         call->ev_join = ss->join;
         CAEE_TRY(order(ss->fork, s, ss->stream, "fork to the side stream"));
-        sb = call->side;
+        s_small = call->side;
     }
     // Gate/up skips the shared experts when the routing launch ran them.
     FfnParams pg = p;
     pg.skip_shared = call->shared_done ? 1 : 0;
-    // One list's chain: gate/up, (fp8) quantisation of its SwiGLU rows, down.
-    // The 8-bit GEMM reads its rows' block scales transposed and in permuted
-    // row order: gathered once for x, written so by the quantiser for H.
+    // One list's chain: gate/up, (fp8) quantisation of its SwiGLU rows (the
+    // prefill kernel's gate/up writes them quantised), down.
     auto chain = [&](int list, int nb, hipStream_t st) -> caee_status_t {
-        const bool gemm = d->w_dtype == CAEE_FP8_E4M3 && nb == gemm_fp8_blocks() && gemm_fp8_applies(*d, p.tiled);
-        FfnParams q = p;
-        q.list = list;
-        if (gemm)
-            CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, st, "gather x scales",
-                                  [&] { return launch_gather_xs(q, L.max_chunks, st); }));
         CAEE_TRY(gate_up_list(d, pg, list, nb, L.max_chunks, st));
-        if (d->w_dtype == CAEE_FP8_E4M3 && !(gemm && gemm_fp8_fuses_quant()))
+        if (d->w_dtype == CAEE_FP8_E4M3 && !(list == 1 && gemm8)) {
+            FfnParams q = p;
+            q.list = list;
             CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, st, "quantise H",
-                                  [&] { return launch_quant_list(q, nb, L.max_chunks, gemm, st); }));
+                                  [&] { return launch_quant_list(q, nb, L.max_chunks, st); }));
+        }
         return down_list(d, p, list, nb, L.max_chunks, st);
     };
-    if (nb_big) CAEE_TRY(chain(1, nb_big, sb));
-    return chain(0, nb_small, s);
+    if (nb_big) CAEE_TRY(chain(1, nb_big, s));
+    return all_big ? CAEE_OK : chain(0, nb_small, s_small);
 }
 
 caee_status_t ffn_end(const FfnParams& p, FfnCall* call) {
@@ -402,12 +414,13 @@ caee_status_t check_layer_args(const caee_layer_desc_t* desc, const void* x, con
     return CAEE_OK;
 }
 
-// The whole layer on validated arguments and a checked workspace; the big
-// chunks run on a second stream when `side` is set.
+// The whole layer on validated arguments and a checked workspace; the small
+// chunks run on a second stream next to the big ones when `side` is set.
 caee_status_t moe_layer_run(const caee_layer_desc_t* desc, const void* x, const float* logits, const float* bias,
                             const float* cost, const int32_t* bin, const caee_expert_weights_t* weights, void* y,
                             const caee_route_out_t* out, char* wsb, const WsLayout& L, hipStream_t s, bool side) {
     RouteParams p = make_route_params(desc, logits, bias, cost, bin, wsb, L);
+    p.chunk_small = call_chunk_small(*desc, weights->layout == CAEE_LAYOUT_TILED);
     p.chunk_big = call_chunk_big(*desc, weights->layout == CAEE_LAYOUT_TILED);
     set_route_outputs(p, out, wsb, L);
     const FfnParams fp = make_ffn_params(desc, x, p.topk_ids, p.topk_w, weights, y, wsb, L);
@@ -423,7 +436,10 @@ caee_status_t moe_layer_run(const caee_layer_desc_t* desc, const void* x, const 
 // holds its own copy at its own address), never freed.  In host code the
 // array's name is not a device address; every host use goes through the
 // address hipGetSymbolAddress returns for the current device.
-__device__ __align__(256) unsigned char scratch[CAEE_SCRATCH_BYTES];
+// It is 1/64 larger than CAEE_SCRATCH_BYTES: the transposed block scales of
+// 8-bit batches of 33 to 256 tokens take at most that share of the rest of a
+// workspace, and do not count against the limit.
+__device__ __align__(256) unsigned char scratch[CAEE_SCRATCH_BYTES + CAEE_SCRATCH_BYTES / 64 + 1024];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -500,6 +516,7 @@ caee_status_t caee_expert_ffn(const caee_layer_desc_t* desc, const void* x, cons
     CAEE_TRY(check_ws(desc, ws, ws_bytes, &L));
     if (desc->T == 0) return CAEE_OK;
     RouteParams p = make_route_params(desc, nullptr, nullptr, nullptr, nullptr, (char*)ws, L);
+    p.chunk_small = call_chunk_small(*desc, weights->layout == CAEE_LAYOUT_TILED);
     p.chunk_big = call_chunk_big(*desc, weights->layout == CAEE_LAYOUT_TILED);
     p.topk_ids = const_cast<int32_t*>(topk_ids);
     p.do_permute = 1;
@@ -530,9 +547,9 @@ caee_status_t caee_moe_layer_noalloc(const caee_layer_desc_t* desc, const void* 
     g_last_error.clear();
     CAEE_TRY(check_layer_args(desc, x, logits, bias, cost, bin, weights, y, out));
     const WsLayout L = ws_layout(*desc);
-    if (L.total > (size_t)CAEE_SCRATCH_BYTES)
+    if (L.total - L.decode_scales > (size_t)CAEE_SCRATCH_BYTES)
         return fail(CAEE_ERR_UNSUPPORTED, "the call needs %zu bytes of scratch; the library's array holds %zu "
-                    "(use caee_moe_layer with a workspace)", L.total, (size_t)CAEE_SCRATCH_BYTES);
+                    "(use caee_moe_layer with a workspace)", L.total - L.decode_scales, (size_t)CAEE_SCRATCH_BYTES);
     if (desc->T == 0) return CAEE_OK;
     void* at = nullptr;
     CAEE_TRY(scratch_address(&at));

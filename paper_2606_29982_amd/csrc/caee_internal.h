@@ -36,11 +36,17 @@ constexpr int kMaxTokenBlocks = CAEE_MAX_TOKEN_BLOCKS;
 constexpr int kPrefillT = CAEE_PREFILL_T;
 // 8-bit batches above this many tokens run their big chunks (as wide as its
 // token tile: 256 rows) with the prefill kernel of ffn_prefill8.hip, when the
-// weights are tiled and the sizes fit (0 disables it).
+// weights are tiled and the sizes fit.  Up to 32 tokens there are no big
+// chunks; from 33 on one such item (256 weight rows, the whole contraction)
+// takes about 90 us where the LDS-staged 64-row kernels took 500 us for a
+// popular expert's gate/up (R1-shaped layer, skewed T = 128: 667 -> 555 us,
+// skewed T = 250: 1057 -> 823 us; evenly used experts at T = 64 .. 200: -2 to +1 %).
 #ifndef CAEE_GEMM_T
-#define CAEE_GEMM_T 256
+#define CAEE_GEMM_T 32
 #endif
 constexpr int kGemmT = CAEE_GEMM_T;
+// Row-major 8-bit batches above this many tokens take 128-row staged chunks.
+constexpr int kStagedWideT = 256;
 // bf16 big chunks (experts with more rows than a small chunk holds) run
 // the same LDS-pipelined GEMM, as wide as its token tile (0 disables).
 #ifndef CAEE_GEMM_BF16
@@ -99,7 +105,7 @@ constexpr int kDownU1 = CAEE_DOWN_U1;
 #define CAEE_BIG_STAGED 1
 #endif
 constexpr bool kBigStaged = CAEE_BIG_STAGED != 0;
-// Run the big-chunk launches on a second stream, concurrently with the small ones.
+// Run the small-chunk launches on a second stream, concurrently with the big ones.
 #ifndef CAEE_BIG_CONCURRENT
 #define CAEE_BIG_CONCURRENT 1
 #endif
@@ -133,6 +139,7 @@ struct WsLayout {
     size_t hq, hs;              // fp8 path: [P][f] e4m3 codes of H and [P][f/128] fp32 scales
     size_t xst, hst;            // fp8 GEMM: [d/128][P] and [f/128][P] block scales of the permuted rows
     size_t total;
+    size_t decode_scales;       // the part of it that xst and hst take in batches of up to kStagedWideT tokens
     int P, max_chunks, ksplit;
     int chunk_small;            // an expert slot with at most this many rows is one small chunk
     int chunk_big;              // rows of a big chunk at most
@@ -197,15 +204,21 @@ inline int small_token_blocks(const caee_layer_desc_t& d) { return d.T <= 16 ? 1
 inline int big_token_blocks(const caee_layer_desc_t& d) {
     if (d.T <= 16 * small_token_blocks(d)) return 0;
     int nb = d.T <= kPrefillT ? 4 : 8;
-    if (kGemmT > 0 && d.w_dtype == CAEE_FP8_E4M3 && d.T > kGemmT) nb = 8;
+    if (d.w_dtype == CAEE_FP8_E4M3 && d.T > kStagedWideT) nb = 8;
     return nb < kMaxTokenBlocks ? nb : kMaxTokenBlocks;
 }
 
+#ifndef CAEE_ALL_BIG_FP8
+#define CAEE_ALL_BIG_FP8 8
+#endif
+#ifndef CAEE_ALL_BIG_BF16
+#define CAEE_ALL_BIG_BF16 16
+#endif
+constexpr int kAllBigRowsFp8 = CAEE_ALL_BIG_FP8, kAllBigRowsBf16 = CAEE_ALL_BIG_BF16;   // see call_chunk_small
 bool gemm_fp8_applies(const caee_layer_desc_t& d, bool tiled);
 bool gemm_bf16_applies(const caee_layer_desc_t& d, bool tiled);
 int gemm_fp8_blocks();         // 16-token blocks of an 8-bit big chunk
 int gemm_bf16_blocks();        // 16-token blocks of a bf16 big chunk
-bool gemm_fp8_fuses_quant();   // the GEMM's gate/up writes the e4m3 H rows itself
 
 // 16-token column blocks of a call's big chunks: the width of the 8-bit
 // GEMM's tile when that kernel runs the call's big list (its chunks are as
@@ -217,6 +230,24 @@ inline int call_big_blocks(const caee_layer_desc_t& d, bool tiled) {
     if (nb > 0 && gemm_fp8_applies(d, tiled)) return gemm_fp8_blocks();
     if (nb > 0 && gemm_bf16_applies(d, tiled)) return gemm_bf16_blocks();
     return nb;
+}
+
+// Most rows of a small chunk in a call; 0: every chunk is a big one, and the
+// small-chunk kernels are not launched.  The small-chunk kernels read each
+// token block once per weight tile from L2, the big-chunk ones once per
+// workgroup through LDS, but a big-chunk item is a workgroup wide, so with few
+// chunks the last round of items is nearly empty.  The line lies at a mean
+// number of rows per routed expert (R1-shaped layer, evenly used experts):
+//   8-bit: T = 200 (6.25 rows) 1914 us with small chunks, 1923 without;
+//          T = 400 (12.5) 2299 / 2024; T = 600 (18.8) 2810 / 2051;
+//          T = 1000 (31) 2754 / 2189; T = 2500 equal;
+//   bf16:  T = 300 (9.4) 3583 / 3918; T = 800 (25) 4643 / 4065; T = 2048 equal.
+inline int call_chunk_small(const caee_layer_desc_t& d, bool tiled) {
+    const int nb = big_token_blocks(d);
+    const long long pairs = (long long)d.T * d.k;
+    if (nb > 0 && gemm_fp8_applies(d, tiled) && pairs >= (long long)kAllBigRowsFp8 * d.E) return 0;
+    if (nb > 0 && gemm_bf16_applies(d, tiled) && pairs >= (long long)kAllBigRowsBf16 * d.E) return 0;
+    return 16 * small_token_blocks(d);
 }
 
 // Rows per big chunk of a call (16 when there are no big chunks).
@@ -260,11 +291,12 @@ inline WsLayout ws_layout(const caee_layer_desc_t& d) {
     L.xs = take(fp8 ? T * (d.d / 128) * 4 : 0);
     L.hq = take(fp8 ? size_t(L.P) * d.f : 0);
     L.hs = take(fp8 ? size_t(L.P) * (d.f / 128) * 4 : 0);
-    const bool gemm = fp8 && kGemmT > 0 && d.T > kGemmT;
+    const bool gemm = fp8 && d.T > kGemmT;
     L.xst = take(gemm ? size_t(L.P) * (d.d / 128) * 4 : 0);
     L.hst = take(gemm ? size_t(L.P) * (d.f / 128) * 4 : 0);
     L.ksplit = gate_up_split(d);
     L.total = off;
+    L.decode_scales = d.T <= kStagedWideT ? off - L.xst : 0;
     return L;
 }
 
@@ -428,7 +460,7 @@ hipError_t launch_combine(const FfnParams& p, hipStream_t s);
 hipError_t launch_quant_rows(const void* src, int src_bf16, long long rows, int cols, uint8_t* q, float* scale,
                              hipStream_t s);
 hipError_t launch_gate_up_fp8(const FfnParams& p, int nb, int max_chunks, hipStream_t s);
-hipError_t launch_quant_list(const FfnParams& p, int nb, int max_chunks, bool transposed, hipStream_t s);
+hipError_t launch_quant_list(const FfnParams& p, int nb, int max_chunks, hipStream_t s);
 hipError_t launch_gather_xs(const FfnParams& p, int max_chunks, hipStream_t s);
 bool gemm_fp8_supports(const FfnParams& p, int nb);
 bool gemm_bf16_supports(const FfnParams& p, int nb);
@@ -461,8 +493,8 @@ void set_route_outputs(RouteParams& p, const caee_route_out_t* out, char* ws, co
 
 // The FFN of one layer call, in three parts:
 //   ffn_begin   (fp8) quantises x;
-//   ffn_routed  after the permutation, runs the small chunks on the main
-//               stream and (big_on_side) the big chunks on a side stream
+//   ffn_routed  after the permutation, runs the big chunks on the main
+//               stream and (two_streams) the small chunks on a side stream
 //               forked from it; with p.pass_of set only pass p.pass_id runs;
 //   ffn_end     joins the side stream and combines into y.
 struct FfnCall {
@@ -473,7 +505,7 @@ struct FfnCall {
 caee_status_t ffn_begin(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, hipStream_t s,
                         FfnCall* call);
 caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, FfnCall* call,
-                         bool big_on_side);
+                         bool two_streams);
 caee_status_t ffn_end(const FfnParams& p, FfnCall* call);
 
 // Opt-in timing: events bracket each launch on the caller's stream.

@@ -58,9 +58,7 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* src, int src_bf1
 
 // The fp32 SwiGLU rows of the chunks of one work list (at most rows_max
 // rows per chunk), so that each list's chain can run on its own stream.
-// Scales go to hs ([row][block]), or transposed to hst ([block][row]) for
-// the 8-bit GEMM.
-__global__ __launch_bounds__(256) void k_quant_list(FfnParams p, int rows_max, int transposed) {
+__global__ __launch_bounds__(256) void k_quant_list(FfnParams p, int rows_max) {
     const int lane = threadIdx.x & (kWave - 1);
     const int nblk = p.f / 128;
     const long long per_chunk = (long long)rows_max * nblk;
@@ -71,8 +69,7 @@ __global__ __launch_bounds__(256) void k_quant_list(FfnParams p, int rows_max, i
         const int r = rem / nblk;
         const ChunkRef ck = ffn_chunk(p, c);
         if (r >= ck.ntok) continue;
-        if (transposed) quant_block(p.h, 0, ck.row0 + r, rem - r * nblk, p.f, p.hq, p.hst, 1, p.P, lane);
-        else quant_block(p.h, 0, ck.row0 + r, rem - r * nblk, p.f, p.hq, p.hs, nblk, 1, lane);
+        quant_block(p.h, 0, ck.row0 + r, rem - r * nblk, p.f, p.hq, p.hs, nblk, 1, lane);
     }
 }
 
@@ -549,13 +546,13 @@ hipError_t launch_quant_rows(const void* src, int src_bf16, long long rows, int 
     return hipGetLastError();
 }
 
-hipError_t launch_quant_list(const FfnParams& p, int nb, int max_chunks, bool transposed, hipStream_t s) {
+hipError_t launch_quant_list(const FfnParams& p, int nb, int max_chunks, hipStream_t s) {
     const long long waves = (long long)max_chunks * 16 * nb * (p.f / 128);
     long long blocks = (waves + 3) / 4;
     const long long cap = (long long)device_cu_count() * 16;
     if (blocks > cap) blocks = cap;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_quant_list, dim3((unsigned)blocks), dim3(256), 0, s, p, 16 * nb, transposed ? 1 : 0);
+    hipLaunchKernelGGL(k_quant_list, dim3((unsigned)blocks), dim3(256), 0, s, p, 16 * nb);
     return hipGetLastError();
 }
 
