@@ -325,7 +325,7 @@ caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const W
         FfnParams pb = p;
         pb.list = 1;
         CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, s, "gather x scales",
-                              [&] { return launch_gather_xs(pb, L.max_chunks, s); }));
+                              [&] { return launch_gather_xs(pb, L.grid_chunks, s); }));
     }
     // The small chunks (many, bandwidth-bound) run on a side stream next to
     // the big ones (few, long work items): disjoint rows.  The fork comes
@@ -349,14 +349,14 @@ caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const W
     // One list's chain: gate/up, (fp8) quantisation of its SwiGLU rows (the
     // prefill kernel's gate/up writes them quantised), down.
     auto chain = [&](int list, int nb, hipStream_t st) -> caee_status_t {
-        CAEE_TRY(gate_up_list(d, pg, list, nb, L.max_chunks, st));
+        CAEE_TRY(gate_up_list(d, pg, list, nb, L.grid_chunks, st));
         if (d->w_dtype == CAEE_FP8_E4M3 && !(list == 1 && gemm8)) {
             FfnParams q = p;
             q.list = list;
             CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, st, "quantise H",
-                                  [&] { return launch_quant_list(q, nb, L.max_chunks, st); }));
+                                  [&] { return launch_quant_list(q, nb, L.grid_chunks, st); }));
         }
-        return down_list(d, p, list, nb, L.max_chunks, st);
+        return down_list(d, p, list, nb, L.grid_chunks, st);
     };
     if (nb_big) CAEE_TRY(chain(1, nb_big, s));
     return all_big ? CAEE_OK : chain(0, nb_small, s_small);

@@ -425,9 +425,9 @@ __global__ __launch_bounds__(256) void k_combine(FfnParams p) {
     }
 }
 
-int grid_for(long long waves_needed) {
+int grid_for(long long waves_needed, int per_cu) {
     const long long wgs = (waves_needed + 3) / 4;
-    const long long cap = (long long)device_cu_count() * 8;
+    const long long cap = (long long)device_cu_count() * per_cu;
     return (int)(wgs < 1 ? 1 : (wgs < cap ? wgs : cap));
 }
 
@@ -473,12 +473,12 @@ hipError_t launch_big(const FfnParams& p, bool gate_up, int nb, dim3 grid, hipSt
 hipError_t launch_gate_up(const FfnParams& p, int w_dtype, int nb, int max_chunks, hipStream_t s) {
     if (w_dtype == CAEE_BF16 && gemm_bf16_supports(p, nb)) return launch_gemm(p, true, max_chunks, s);
     if (nb >= 4 && kBigStaged) {
-        const dim3 grid(grid_for((long long)max_chunks * (p.f / 16)));
+        const dim3 grid(grid_for((long long)max_chunks * (p.f / 16), 8));
         if (w_dtype == CAEE_BF16) return launch_big<Bf16Math>(p, true, nb, grid, s);
         if (w_dtype == CAEE_F32) return launch_big<F32Math>(p, true, nb, grid, s);
         return hipErrorInvalidValue;
     }
-    const dim3 grid(grid_for((long long)max_chunks * (p.f / 16) * p.ksplit));   // waves wanted
+    const dim3 grid(grid_for((long long)max_chunks * (p.f / 16) * p.ksplit, kSmallGridPerCu));   // waves wanted
     if (w_dtype == CAEE_BF16) return launch_nb<Bf16Math, GateUpK, kGateUpU1, kGateUpU>(p, nb, grid, s);
     if (w_dtype == CAEE_F32) return launch_nb<F32Math, GateUpK, kGateUpU1, kGateUpU>(p, nb, grid, s);
     return hipErrorInvalidValue;
@@ -487,12 +487,12 @@ hipError_t launch_gate_up(const FfnParams& p, int w_dtype, int nb, int max_chunk
 hipError_t launch_down(const FfnParams& p, int w_dtype, int nb, int max_chunks, hipStream_t s) {
     if (w_dtype == CAEE_BF16 && gemm_bf16_supports(p, nb)) return launch_gemm(p, false, max_chunks, s);
     if (nb >= 4 && kBigStaged) {
-        const dim3 grid(grid_for((long long)max_chunks * (p.d / 16) / 2));
+        const dim3 grid(grid_for((long long)max_chunks * (p.d / 16) / 2, 8));
         if (w_dtype == CAEE_BF16) return launch_big<Bf16Math>(p, false, nb, grid, s);
         if (w_dtype == CAEE_F32) return launch_big<F32Math>(p, false, nb, grid, s);
         return hipErrorInvalidValue;
     }
-    const dim3 grid(grid_for((long long)max_chunks * (p.d / 16)));
+    const dim3 grid(grid_for((long long)max_chunks * (p.d / 16), kSmallGridPerCu));
     if (w_dtype == CAEE_BF16) return launch_nb<Bf16Math, DownK, kDownU1, kDownU>(p, nb, grid, s);
     if (w_dtype == CAEE_F32) return launch_nb<F32Math, DownK, kDownU1, kDownU>(p, nb, grid, s);
     return hipErrorInvalidValue;

@@ -529,9 +529,9 @@ __global__ __launch_bounds__(kFfnThreads) void k_down_fp8_big(FfnParams p) {
     }
 }
 
-int grid_for_waves(long long waves_needed) {
+int grid_for_waves(long long waves_needed, int per_cu) {
     const long long wgs = (waves_needed + 3) / 4;
-    const long long cap = (long long)device_cu_count() * 8;
+    const long long cap = (long long)device_cu_count() * per_cu;
     return (int)(wgs < 1 ? 1 : (wgs < cap ? wgs : cap));
 }
 
@@ -559,13 +559,13 @@ hipError_t launch_quant_list(const FfnParams& p, int nb, int max_chunks, hipStre
 hipError_t launch_gate_up_fp8(const FfnParams& p, int nb, int max_chunks, hipStream_t s) {
     if (gemm_fp8_supports(p, nb)) return launch_prefill8(p, true, max_chunks, s);
     if (nb >= 4 && kBigStaged) {
-        const dim3 grid(grid_for_waves((long long)max_chunks * (p.f / 16) / CAEE_FP8_BIG_TW_GU));
+        const dim3 grid(grid_for_waves((long long)max_chunks * (p.f / 16) / CAEE_FP8_BIG_TW_GU, 8));
         if (nb == 4) hipLaunchKernelGGL(k_gate_up_fp8_big<4>, grid, dim3(kFfnThreads), 0, s, p);
         else if (nb == 8) hipLaunchKernelGGL(k_gate_up_fp8_big<8>, grid, dim3(kFfnThreads), 0, s, p);
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
-    const dim3 grid(grid_for_waves((long long)max_chunks * (p.f / 16) * p.ksplit));
+    const dim3 grid(grid_for_waves((long long)max_chunks * (p.f / 16) * p.ksplit, kSmallGridPerCu));
     switch (nb) {
         case 1: ffn_launch(k_gate_up_fp8<1>, grid, dim3(kFfnThreads), s, p); break;
         case 2: ffn_launch(k_gate_up_fp8<2>, grid, dim3(kFfnThreads), s, p); break;
@@ -579,13 +579,13 @@ hipError_t launch_gate_up_fp8(const FfnParams& p, int nb, int max_chunks, hipStr
 hipError_t launch_down_fp8(const FfnParams& p, int nb, int max_chunks, hipStream_t s) {
     if (gemm_fp8_supports(p, nb)) return launch_prefill8(p, false, max_chunks, s);
     if (nb >= 4 && kBigStaged) {
-        const dim3 grid(grid_for_waves((long long)max_chunks * (p.d / 16) / CAEE_FP8_BIG_TW_DN));
+        const dim3 grid(grid_for_waves((long long)max_chunks * (p.d / 16) / CAEE_FP8_BIG_TW_DN, 8));
         if (nb == 4) hipLaunchKernelGGL(k_down_fp8_big<4>, grid, dim3(kFfnThreads), 0, s, p);
         else if (nb == 8) hipLaunchKernelGGL(k_down_fp8_big<8>, grid, dim3(kFfnThreads), 0, s, p);
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
-    const dim3 grid(grid_for_waves((long long)max_chunks * (p.d / 16)));
+    const dim3 grid(grid_for_waves((long long)max_chunks * (p.d / 16), kSmallGridPerCu));
     switch (nb) {
         case 1: hipLaunchKernelGGL(k_down_fp8<1>, grid, dim3(kFfnThreads), 0, s, p); break;
         case 2: hipLaunchKernelGGL(k_down_fp8<2>, grid, dim3(kFfnThreads), 0, s, p); break;
