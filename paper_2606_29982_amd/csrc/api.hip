@@ -197,7 +197,7 @@ RouteParams make_route_params(const caee_layer_desc_t* d, const float* logits, c
     p.refill = d->refill;
     p.seed = d->seed;
     p.keep_top1 = d->keep_top1;
-    p.counters = (int32_t*)(ws + L.counters);
+    p.counts = (int32_t*)(ws + L.counts);
     p.chunk_small = L.chunk_small;
     p.chunk_big = L.chunk_big;
     p.orig_ids = (int32_t*)(ws + L.orig);
@@ -373,6 +373,7 @@ void set_route_outputs(RouteParams& p, const caee_route_out_t* out, char* ws, co
     if (out && out->orig_ids) p.orig_ids = out->orig_ids;
     p.masks = out ? out->masks : nullptr;
     p.stats = out ? out->stats : nullptr;
+    if (p.stats) p.counts = p.stats + 6;
     p.bin_loads = out ? out->bin_loads : nullptr;
 }
 
@@ -491,12 +492,7 @@ caee_status_t caee_route_prune(const caee_layer_desc_t* desc, const float* logit
     CAEE_TRY(check_ws(desc, ws, ws_bytes, &L));
     if (desc->T == 0) return CAEE_OK;
     RouteParams p = make_route_params(desc, logits, bias, cost, bin, (char*)ws, L);
-    p.topk_ids = out->topk_ids;
-    p.topk_w = out->topk_w;
-    if (out->orig_ids) p.orig_ids = out->orig_ids;
-    p.masks = out->masks;
-    p.stats = out->stats;
-    p.bin_loads = out->bin_loads;
+    set_route_outputs(p, out, (char*)ws, L);
     p.do_permute = 0;
     hipStream_t s = as_stream(stream);
     return timed_launch(CAEE_KERNEL_ROUTE, s, "route", [&] { return launch_route(p, s); });

@@ -135,7 +135,7 @@ struct WsLayout {
     size_t trans;               // [E] uint8 membership of A_trans
     size_t mflag;               // [T][k] uint8: the (token, slot) pair is mandatory on its own
     size_t imp_sum;             // [E] float64 batch-summed gate weight (SUM rule)
-    size_t counters;            // [4] int: (unused), refilled slots, empty slots
+    size_t counts;              // [2] int: refilled and empty slots when the caller takes no stats
     size_t perm_off;            // [E + n_shared + 1] first permuted row of each expert slot
     size_t perm_tok;            // [P] token of each permuted row
     size_t perm_pos;            // [T][k + n_shared] permuted row of each (token, slot), -1 unused
@@ -288,7 +288,7 @@ inline WsLayout ws_layout(const caee_layer_desc_t& d) {
     L.trans = take(d.E);
     L.mflag = take(T * d.k);
     L.imp_sum = take(size_t(d.E) * 8);
-    L.counters = take(16);
+    L.counts = take(16);
     L.perm_off = take(size_t(d.E + d.n_shared + 1) * 4);
     L.perm_tok = take(size_t(L.P) * 4);
     L.perm_pos = take(T * slots * 4);
@@ -341,7 +341,7 @@ struct RouteParams {
     uint8_t* trans;
     uint8_t* mflag;
     double* imp_sum;
-    int32_t* counters;
+    int32_t* counts;    // refilled and empty slots (stats[6], stats[7] when there are stats)
     int chunk_small, chunk_big;
     // permutation outputs
     int32_t* perm_off;
@@ -351,7 +351,8 @@ struct RouteParams {
     int32_t* chunks;
     int32_t* n_chunks;
     double* sslot;      // scores s of each token's K_t slots [T][k] when kept by routing (else recomputed)
-    int do_permute;     // 0: the permutation kernel only reports the refill/empty-slot counts
+    int pair_stats;     // imp_sum and trans hold each expert's importance and flags (k_expert_stats)
+    int do_permute;     // 0: routing only
 };
 
 struct FfnParams {

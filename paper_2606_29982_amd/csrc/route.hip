@@ -73,7 +73,7 @@ __device__ inline double dpp_upd_d(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Wave-wide max and min, all in VALU: butterfly inside each 16-lane row,
+// Wave-wide max, all in VALU: butterfly inside each 16-lane row,
 // then row 1 takes row 0's result and row 3 row 2's, then row 3 takes row
 // 1's; lane 63 ends with the wave's result, which every lane reads.
 __device__ inline double wave_max_d(double v) {
@@ -85,16 +85,6 @@ __device__ inline double wave_max_d(double v) {
     v = fmax(v, dpp_upd_d<kDppRowBcast31, 0xC>(v));
     return readlane_d(v, 63);
 }
-__device__ inline int wave_min_i(int v) {
-    v = min(v, dpp_i<kDppXor1>(v));
-    v = min(v, dpp_i<kDppXor2>(v));
-    v = min(v, dpp_i<kDppHalfMirror>(v));
-    v = min(v, dpp_i<kDppMirror>(v));
-    v = min(v, dpp_upd_i<kDppRowBcast15, 0xA>(v));
-    v = min(v, dpp_upd_i<kDppRowBcast31, 0xC>(v));
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
 // Inclusive prefix sum over the 64 lanes, in VALU: shifts by 1, 2, 4, 8
 // within each row (lanes shifted in from outside the row read 0), then
 // rows 1 and 3 add the last lane of rows 0 and 2, rows 2 and 3 that of row 1.
@@ -108,12 +98,76 @@ __device__ inline int wave_incl_scan(int v) {
     return v;
 }
 
-// Wave-wide argmax of (v, i): the largest v, and among the lanes holding it
-// the lowest i (the same result as merging pairs in any order).  Values are
-// never NaN.  Every lane gets the result.
-__device__ inline void wave_argmax(double& v, int& i) {
-    const double m = wave_max_d(v);
-    i = wave_min_i(v == m ? i : kNoIdx);
+// The bits of a double as an unsigned integer in the same order (no NaN);
+// 0 stands for "none" below every value.
+__device__ inline unsigned long long sortable(double v) {
+    const long long b = __double_as_longlong(v);
+    return (unsigned long long)b ^ ((unsigned long long)(b >> 63) | 0x8000000000000000ull);
+}
+
+// Wave-wide max of unsigned words: the same moves as wave_max_d, each one
+// instruction with its max.
+template <int C, int RM>
+__device__ inline unsigned dpp_max_u(unsigned v) {
+    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, C, RM, 0xF, false));
+}
+__device__ inline unsigned wave_max_u(unsigned v) {
+    v = dpp_max_u<kDppXor1, 0xF>(v);
+    v = dpp_max_u<kDppXor2, 0xF>(v);
+    v = dpp_max_u<kDppHalfMirror, 0xF>(v);
+    v = dpp_max_u<kDppMirror, 0xF>(v);
+    v = dpp_max_u<kDppRowBcast15, 0xA>(v);
+    v = dpp_max_u<kDppRowBcast31, 0xC>(v);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Lane holding the largest v, the lowest such lane on ties; -1 when every
+// lane holds 0.  The high words decide unless they tie.  (Experts are spread
+// over the lanes in index order, so the lowest lane holds the lowest index.
+// With float64 max and an index min, 12 double-word moves a pick, a top-8
+// selection took 2.2 us of a one-token call.)
+__device__ inline int wave_argmax_lane(unsigned long long v) {
+    const unsigned hi = (unsigned)(v >> 32), lo = (unsigned)v;
+    const unsigned mh = wave_max_u(hi);
+    if (mh == 0u) return -1;   // (0 in the high word is below every value's)
+    unsigned long long m = __ballot(hi == mh);
+    if (m & (m - 1ull)) {
+        const unsigned ml = wave_max_u(hi == mh ? lo : 0u);
+        m = __ballot(hi == mh && lo == ml);
+    }
+    return __ffsll((long long)m) - 1;
+}
+
+// Largest of the lane's open keys (0 if none) and which one it is.
+template <int EPL>
+__device__ inline unsigned long long lane_best(const unsigned long long (&key)[EPL], const bool (&open)[EPL],
+                                               int& which) {
+    unsigned long long v = 0ull;
+    which = 0;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+        if (open[i] && key[i] > v) {
+            v = key[i];
+            which = i;
+        }
+    }
+    return v;
+}
+
+// Argmax of (v, i) over the first 16 lanes: the largest v, and among the
+// lanes holding it the lowest i.  Values are never NaN; lanes 0 to 15 get the
+// result.
+__device__ inline void row_argmax(double& v, int& i) {
+    double m = v;
+    m = fmax(m, dpp_d<kDppXor1>(m));
+    m = fmax(m, dpp_d<kDppXor2>(m));
+    m = fmax(m, dpp_d<kDppHalfMirror>(m));
+    m = fmax(m, dpp_d<kDppMirror>(m));
+    i = v == m ? i : kNoIdx;
+    i = min(i, dpp_i<kDppXor1>(i));
+    i = min(i, dpp_i<kDppXor2>(i));
+    i = min(i, dpp_i<kDppHalfMirror>(i));
+    i = min(i, dpp_i<kDppMirror>(i));
     v = m;
 }
 
@@ -208,34 +262,31 @@ __device__ void route_token(const RouteParams& p, int t, int lane, int* ids, dou
         }
         gsel = lane_valid && rank < p.topk_group;
     } else {
+        const unsigned long long gk = lane_valid ? sortable(gscore) : 0ull;
         for (int r = 0; r < p.topk_group; ++r) {
-            double v = (lane_valid && !gsel) ? gscore : -INFINITY;
-            int gi = (lane_valid && !gsel) ? my_group : kNoIdx;
-            wave_argmax(v, gi);
-            if (my_group == gi) gsel = true;
+            const int l = max(wave_argmax_lane(gsel ? 0ull : gk), 0);
+            if (lane_valid && my_group == __builtin_amdgcn_readlane(my_group, l)) gsel = true;
         }
     }
 
     // Top-k keys of the selected groups; lane r keeps the r-th pick.
-    bool chosen[EPL];
+    bool open[EPL];
+    unsigned long long ukey[EPL];
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) chosen[i] = false;
+    for (int i = 0; i < EPL; ++i) {
+        open[i] = gsel;
+        ukey[i] = sortable(key[i]);
+    }
     int my_id = kNoIdx;
     double my_s = 0.0;
     for (int r = 0; r < p.k; ++r) {
-        double v = -INFINITY;
-        int ei = kNoIdx;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            if (gsel && !chosen[i] && key[i] > v) {
-                v = key[i];
-                ei = lane * EPL + i;
-            }
-        }
-        wave_argmax(v, ei);
+        int which;
+        // (k keys are always open; the max only guards against NaN inputs)
+        const int l = max(wave_argmax_lane(lane_best<EPL>(ukey, open, which)), 0);
 #pragma unroll
         for (int i = 0; i < EPL; ++i)
-            if (lane * EPL + i == ei) chosen[i] = true;
+            if (lane == l && i == which) open[i] = false;
+        const int ei = l * EPL + __builtin_amdgcn_readlane(which, l);
         if (lane == r) my_id = ei;
     }
     my_s = fetch_score<EPL>(s, my_id, lane < p.k, p.E);
@@ -247,7 +298,7 @@ __device__ void route_token(const RouteParams& p, int t, int lane, int* ids, dou
     const double g = my_s / total;
     double bg = mine ? g : -INFINITY;
     int best = mine ? my_id : kNoIdx;
-    wave_argmax(bg, best);   // the token's top expert by G, ties to the lower index
+    row_argmax(bg, best);   // the token's top expert by G, ties to the lower index (lanes < k hold the slots)
     // Pairs that are mandatory on their own: the threshold (MAX) or the
     // cumulative-ratio prefix (CIR), and with keep_top1 the token's top expert.
     uint32_t flags = (uint32_t)__ballot(
@@ -296,14 +347,13 @@ template <int EPL>
 __device__ void compensate_token(const RouteParams& p, int t, int lane, const int* orig,
                                  const uint8_t* trans, int* fin, double* sbuf, int* n_refill,
                                  int* n_pad) {
-    bool in_k[EPL], tr[EPL], take[EPL], fin_f[EPL], out_f[EPL];
+    bool in_k[EPL], tr[EPL], out_f[EPL];
     // K_t: lane r < k holds its r-th expert; the list is broadcast lane by lane.
     const int my_orig = lane < p.k ? orig[lane] : -1;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
         in_k[i] = false;
         tr[i] = lane * EPL + i < p.E && trans[lane * EPL + i];
-        take[i] = false;
         out_f[i] = false;
     }
     for (int r = 0; r < p.k; ++r) {
@@ -349,62 +399,64 @@ __device__ void compensate_token(const RouteParams& p, int t, int lane, const in
 
     // Refill order: router key (the paper's compensation) or, for the
     // ablation, a 53-bit random key (exact in a double) per (token, expert).
-    double rv[EPL];
+    // LITERAL: K_final is the top-k of all of A_trans by key, whether in K_t
+    // or not.
+    const bool literal = p.refill == CAEE_REFILL_LITERAL;
+    unsigned long long rv[EPL];
+    bool open[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
         const uint64_t ctr = ((uint64_t)p.seed << 32) | (uint64_t)(t * p.E + lane * EPL + i);
-        rv[i] = p.refill == CAEE_REFILL_RANDOM ? (double)(splitmix64(ctr) >> 11) : key[i];
+        rv[i] = sortable(p.refill == CAEE_REFILL_RANDOM ? (double)(splitmix64(ctr) >> 11) : key[i]);
+        open[i] = tr[i] && (literal || !in_k[i]);
     }
-    // LITERAL: K_final is the top-k of all of A_trans by key (the ordering
-    // pass below), no keep-first refill.
-    const bool literal = p.refill == CAEE_REFILL_LITERAL;
-    const int to_fill = p.refill == CAEE_REFILL_NONE || literal ? 0 : p.k - n_keep;
-    int got = 0;
-    for (int r = 0; r < to_fill; ++r) {
-        double v = -INFINITY;
-        int ei = kNoIdx;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            if (tr[i] && !in_k[i] && !take[i] && rv[i] > v) {
-                v = rv[i];
-                ei = lane * EPL + i;
-            }
+    // The kept experts of K_t in lanes 0 .. n_keep - 1 (rank order), then the
+    // picks, one lane each.
+    int my_id = -1, got = 0;
+    if (!literal) {
+        const int from = __popcll(kept_mask & ((1ull << lane) - 1ull));   // this lane's place if kept
+        for (int r = 0; r < n_keep; ++r) {
+            const int src = __ffsll((long long)__ballot(kept && from == r)) - 1;
+            const int o = __builtin_amdgcn_readlane(my_orig, src);
+            if (lane == r) my_id = o;
         }
-        wave_argmax(v, ei);
-        if (ei == kNoIdx) break;
+    }
+    const int first = literal ? 0 : n_keep;
+    const int to_fill = p.refill == CAEE_REFILL_NONE ? 0 : p.k - first;
+    for (int r = 0; r < to_fill; ++r) {
+        int which;
+        const int l = wave_argmax_lane(lane_best<EPL>(rv, open, which));
+        if (l < 0) break;
 #pragma unroll
         for (int i = 0; i < EPL; ++i)
-            if (lane * EPL + i == ei) take[i] = true;
+            if (lane == l && i == which) {
+                open[i] = false;
+                out_f[i] = true;
+            }
+        const int ei = l * EPL + __builtin_amdgcn_readlane(which, l);
+        if (lane == first + r) my_id = ei;
         ++got;
     }
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) fin_f[i] = literal ? tr[i] : (in_k[i] && tr[i]) || take[i];
-
-    int m = n_keep + got;
-    int my_id = -1;   // lane r: the r-th expert of K_final and its score
-    double my_s = 0.0;
-    if (literal) {
-        int n_tr = 0;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) n_tr += __popcll(__ballot(tr[i]));
-        m = n_tr < p.k ? n_tr : p.k;
-    }
-    for (int r = 0; r < m; ++r) {
-        double v = -INFINITY;
-        int ei = kNoIdx;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            if (fin_f[i] && !out_f[i] && key[i] > v) {
-                v = key[i];
-                ei = lane * EPL + i;
-            }
+    const int m = first + got;
+    // Rank order of K_final (key descending, lower index first): each slot's
+    // lane counts the slots ahead of it.  (LITERAL picked in that order.)
+    if (!literal && got > 0) {
+        const double my_key = fetch_score<EPL>(key, my_id, lane < m, p.E);
+        int ahead = 0;
+        for (int j = 0; j < m; ++j) {
+            const double kj = readlane_d(my_key, j);
+            const int ij = __builtin_amdgcn_readlane(my_id, j);
+            ahead += (kj > my_key || (kj == my_key && ij < my_id)) ? 1 : 0;
         }
-        wave_argmax(v, ei);
-#pragma unroll
-        for (int i = 0; i < EPL; ++i)
-            if (lane * EPL + i == ei) out_f[i] = true;
-        if (lane == r) my_id = ei;
+        int id = -1;
+        for (int j = 0; j < m; ++j) {
+            const int src = __ffsll((long long)__ballot(lane < m && ahead == j)) - 1;
+            const int o = __builtin_amdgcn_readlane(my_id, src);
+            if (lane == j) id = o;
+        }
+        my_id = id;
     }
+    double my_s = 0.0;
     my_s = fetch_score<EPL>(s, my_id, lane < m, p.E);
     if (literal) {   // slots that hold an expert from outside K_t
         got = 0;
@@ -428,60 +480,173 @@ __device__ void compensate_token(const RouteParams& p, int t, int lane, const in
     }
 }
 
-// Routing kernel: one wavefront per token (phase A).  Block 0 also resets
-// the counters the later kernels of this call accumulate into.
+// Routing kernel: one wavefront per token (phase A).
 template <int EPL>
 __global__ __launch_bounds__(kTokThreads) void k_route_tokens(RouteParams p) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int t = blockIdx.x * kTokWaves + wave;
-    if (blockIdx.x == 0 && threadIdx.x < 4) p.counters[threadIdx.x] = 0;
     if (t < p.T)
         route_token<EPL>(p, t, lane, p.orig_ids + (size_t)t * p.k, p.gbuf + (size_t)t * p.k, p.top1 + t,
                          p.mflag + (size_t)t * p.k);
 }
 
-// Batch-summed importance (SUM rule): one wavefront per expert adds the
-// expert's gate weights in ascending token order.
-__device__ void importance_sum_expert(const RouteParams& p, int e, int lane) {
-    double sum = 0.0;
-    for (int t0 = 0; t0 < p.T; t0 += kWave) {
-        const int t = t0 + lane;
-        double v = 0.0;
-        bool hit = false;
-        if (t < p.T) {
-            for (int r = 0; r < p.k; ++r) {
-                if (p.orig_ids[(size_t)t * p.k + r] == e) {
-                    v = p.gbuf[(size_t)t * p.k + r];
-                    hit = true;
+// What pruning needs to know of each routed expert, one workgroup per expert
+// over all tokens: whether any token chose it, whether one of its pairs is
+// mandatory on its own, and its importance -- the largest gate weight (MAX,
+// CIR), or the gate weights added in ascending token order (SUM).
+//
+// Bound by latency: each wave reads its quarter of a tile of tokens, kStatBlk
+// 64-token blocks of K_t at a time (all their loads in flight together), and
+// leaves the gate weights of its hits in LDS in token order; then the SUM
+// rule's one chain of additions runs over LDS (about 9 cycles an addition).
+// A popular expert of a 4096-token batch has thousands of hits, so that chain
+// is what is left: 4096 skewed tokens, SUM: 30 us (one wave per
+// expert reading block after block, readlane per hit: 258 us).
+#ifndef CAEE_PAIR_STATS
+#define CAEE_PAIR_STATS 32768
+#endif
+constexpr int kStatWaves = 4, kStatBlk = 4;
+constexpr int kStatTile = 4096;                       // tokens per tile
+constexpr int kStatWaveTok = kStatTile / kStatWaves;  // a wave's part of it
+constexpr int kStatAct = 1, kStatMust = 2;            // flags left in p.trans
+__global__ __launch_bounds__(kStatWaves * kWave) void k_expert_stats(RouteParams p) {
+    __shared__ __align__(16) double s_g[kStatWaves][kStatWaveTok + 16];   // read up to 16 past the end
+    __shared__ int s_n[kStatWaves];
+    __shared__ double s_max[kStatWaves];
+    __shared__ int s_must[kStatWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int e = blockIdx.x, k = p.k;
+    const bool sum_rule = p.rule == CAEE_IMPORTANCE_SUM;
+    double gmax = 0.0, sum = 0.0;
+    bool any = false, must = false;
+    for (int base = 0; base < p.T; base += kStatTile) {
+        const int t0 = base + wave * kStatWaveTok;
+        const int t1 = min(p.T, t0 + kStatWaveTok);
+        int n = 0;
+        for (int tb = t0; tb < t1; tb += kStatBlk * kWave) {
+            int slot[kStatBlk];
+#pragma unroll
+            for (int u = 0; u < kStatBlk; ++u) slot[u] = -1;
+            if (k % 4 == 0) {   // rows of K_t are 16-byte aligned
+                int4 v[kStatBlk][kMaxK / 4];
+#pragma unroll
+                for (int u = 0; u < kStatBlk; ++u) {
+                    const int t = tb + u * kWave + lane;
+#pragma unroll
+                    for (int q = 0; q < kMaxK / 4; ++q)
+                        v[u][q] = 4 * q < k && t < t1 ? *(const int4*)(p.orig_ids + (size_t)t * k + 4 * q)
+                                                      : make_int4(-1, -1, -1, -1);
+                }
+#pragma unroll
+                for (int u = 0; u < kStatBlk; ++u)
+#pragma unroll
+                    for (int q = 0; q < kMaxK / 4; ++q) {
+                        if (v[u][q].x == e) slot[u] = 4 * q;
+                        if (v[u][q].y == e) slot[u] = 4 * q + 1;
+                        if (v[u][q].z == e) slot[u] = 4 * q + 2;
+                        if (v[u][q].w == e) slot[u] = 4 * q + 3;
+                    }
+            } else {
+                for (int r = 0; r < k; ++r) {
+#pragma unroll
+                    for (int u = 0; u < kStatBlk; ++u) {
+                        const int t = tb + u * kWave + lane;
+                        if (t < t1 && p.orig_ids[(size_t)t * k + r] == e) slot[u] = r;
+                    }
                 }
             }
+            double g[kStatBlk];
+            bool mf[kStatBlk];
+#pragma unroll
+            for (int u = 0; u < kStatBlk; ++u) {
+                const size_t i = (size_t)(tb + u * kWave + lane) * k + (slot[u] < 0 ? 0 : slot[u]);
+                g[u] = slot[u] >= 0 ? p.gbuf[i] : 0.0;
+                mf[u] = slot[u] >= 0 && p.mflag[i];
+            }
+#pragma unroll
+            for (int u = 0; u < kStatBlk; ++u) {
+                const unsigned long long m = __ballot(slot[u] >= 0);
+                gmax = fmax(gmax, g[u]);
+                must |= mf[u];
+                any |= m != 0ull;
+                if (sum_rule && slot[u] >= 0) s_g[wave][n + __popcll(m & ((1ull << lane) - 1ull))] = g[u];
+                n += __popcll(m);
+            }
         }
-        unsigned long long m = __ballot(hit);
-        while (m) {
-            const int l = __ffsll((long long)m) - 1;
-            sum += readlane_d(v, l);
-            m &= m - 1;
+        if (sum_rule) {
+            if (lane == 0) s_n[wave] = n;
+            __syncthreads();
+            if (wave == 0) {   // the same additions on every lane
+                for (int w = 0; w < kStatWaves; ++w) {
+                    const double* sg = s_g[w];
+                    const int m = s_n[w];
+                    // Sixteen values ahead of the additions, read without
+                    // conditions (what lies past the last is not added).
+                    constexpr int kU = 16;
+                    double cur[kU], nxt[kU];
+#pragma unroll
+                    for (int i = 0; i < kU; ++i) cur[i] = sg[i];
+                    int j = 0;
+                    for (; j + kU <= m; j += kU) {
+#pragma unroll
+                        for (int i = 0; i < kU; ++i) nxt[i] = sg[j + kU + i];
+#pragma unroll
+                        for (int i = 0; i < kU; ++i) sum += cur[i];
+#pragma unroll
+                        for (int i = 0; i < kU; ++i) cur[i] = nxt[i];
+                    }
+#pragma unroll
+                    for (int i = 0; i < kU; ++i)
+                        if (j + i < m) sum += cur[i];
+                }
+            }
+            __syncthreads();
         }
     }
-    if (lane == 0) p.imp_sum[e] = sum;
+    gmax = wave_max_d(gmax);
+    const bool wave_must = __ballot(must) != 0ull;
+    if (lane == 0) {
+        s_max[wave] = gmax;
+        s_must[wave] = (any ? kStatAct : 0) | (wave_must ? kStatMust : 0);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double m = 0.0;
+        int f = 0;
+        for (int w = 0; w < kStatWaves; ++w) {
+            m = fmax(m, s_max[w]);
+            f |= s_must[w];
+        }
+        p.imp_sum[e] = sum_rule ? sum : m;
+        p.trans[e] = (uint8_t)f;
+    }
 }
 
-// The same sums for small batches, one thread per expert walking the
+// The SUM rule's sums for small batches, one thread per expert walking the
 // (token, slot) pairs in order (reads of one LDS word by every thread).
 __device__ void importance_sum_small(const RouteParams& p, int tid, int nthr) {
     const int n = p.T * p.k;
     for (int e = tid; e < p.E; e += nthr) {
+        // Pairs of other experts add zero, which changes no sum: the reads need
+        // not wait for a comparison (with a branch per pair 4 us at 64 pairs).
         double sum = 0.0;
-        for (int i = 0; i < n; ++i)
-            if (p.orig_ids[i] == e) sum += p.gbuf[i];
+        int i = 0;
+        constexpr int kU = 8;
+        for (; i + kU <= n; i += kU) {
+            double g[kU];
+            int id[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                id[u] = p.orig_ids[i + u];
+                g[u] = p.gbuf[i + u];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) sum += id[u] == e ? g[u] : 0.0;
+        }
+        for (; i < n; ++i) sum += p.orig_ids[i] == e ? p.gbuf[i] : 0.0;
         p.imp_sum[e] = sum;
     }
-}
-
-__global__ __launch_bounds__(kTokThreads) void k_importance_sum(RouteParams p) {
-    const int e = blockIdx.x * kTokWaves + threadIdx.x / kWave;
-    if (e < p.E) importance_sum_expert(p, e, threadIdx.x & (kWave - 1));
 }
 
 // Pruning kernel (one workgroup): Sec. IV-B steps 1-4 over the whole batch.
@@ -508,38 +673,62 @@ struct PruneShared {
 // Steps 2-3 of Sec. IV-B from the membership in sh.act / sh.must: per-bin
 // loads of A_act and A_must, F_base, the candidates (active, not mandatory)
 // in visiting order (importance descending, index ascending), and the
-// cost-invariant expansion into sh.prom, one bin per thread (bins are
-// independent).  Expects sh.prom, the loads and the candidate count zeroed.
-// Ends with a barrier.
+// cost-invariant expansion into sh.prom, one bin per wave.  Expects sh.prom,
+// the loads and the candidate count zeroed; ends with a barrier unless there
+// are no candidates.
 __device__ void prune_expand(const RouteParams& p, int tid, int nthr, PruneShared& sh) {
     const int lane = tid & (kWave - 1);
     const int wave = tid / kWave;
     const int E = p.E, nb = p.n_bins;
-    for (int e = tid; e < E; e += nthr) {
-        const double c = (double)sh.cost[e];
-        const int b = sh.bin[e];
-        if (sh.act[e] && b >= 0) atomicAdd(&sh.aload[b], c);
-        if (sh.must[e] && b >= 0) atomicAdd(&sh.mload[b], c);
-        if (sh.act[e] && !sh.must[e]) {
-            const int i = atomicAdd(&sh.ncand, 1);
-            sh.cand[i] = e;
-            sh.cimp[i] = sh.imp[e];
+    for (int e0 = wave * kWave; e0 < E; e0 += nthr) {
+        const int e = e0 + lane;
+        const bool act = e < E && sh.act[e], must = e < E && sh.must[e];
+        if (act || must) {
+            const double c = (double)sh.cost[e];
+            const int b = sh.bin[e];
+            if (act && b >= 0) atomicAdd(&sh.aload[b], c);
+            if (must && b >= 0) atomicAdd(&sh.mload[b], c);
+        }
+        // One count per wave; the candidates' order here does not matter.
+        const unsigned long long m = __ballot(act && !must);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(&sh.ncand, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+        if (act && !must) {
+            sh.cand[at] = e;
+            sh.cimp[at] = sh.imp[e];
         }
     }
     __syncthreads();
     const int n_cand = sh.ncand;
-    for (int i = tid; i < n_cand; i += nthr) {
+    if (n_cand == 0) {   // nothing to expand (uniform): A_trans = A_must
+        for (int b = tid; b < nb && p.bin_loads; b += nthr) {
+            p.bin_loads[b] = sh.aload[b];
+            p.bin_loads[nb + b] = p.bin_loads[2 * nb + b] = sh.mload[b];
+        }
+        return;
+    }
+    // Each candidate's rank, counted by kRankLanes neighbouring lanes (one
+    // thread per candidate over 124 of them: 5 us).
+    constexpr int kRankLanes = 8;
+    for (int i0 = tid / kRankLanes; i0 - lane / kRankLanes < n_cand; i0 += nthr / kRankLanes) {
+        const int i = min(i0, n_cand - 1);   // whole waves take part in the moves below
         const int e = sh.cand[i];
         const unsigned long long ie = sh.cimp[i];
         int rank = 0;
-        for (int j = 0; j < n_cand; ++j) {
+        for (int j = lane % kRankLanes; j < n_cand; j += kRankLanes) {
             const unsigned long long io = sh.cimp[j];
             const int o = sh.cand[j];
             rank += (io > ie || (io == ie && o < e)) ? 1 : 0;
         }
-        sh.sorted[rank] = e;
-        sh.cbin[rank] = sh.bin[e];
-        sh.ccost[rank] = sh.cost[e];
+        rank += dpp_i<kDppXor1>(rank);
+        rank += dpp_i<kDppXor2>(rank);
+        rank += dpp_i<kDppHalfMirror>(rank);
+        if (lane % kRankLanes == 0 && i0 < n_cand) {
+            sh.sorted[rank] = e;
+            sh.cbin[rank] = sh.bin[e];
+            sh.ccost[rank] = sh.cost[e];
+        }
     }
     __syncthreads();
     if (wave == 0) {
@@ -554,19 +743,30 @@ __device__ void prune_expand(const RouteParams& p, int tid, int nthr, PruneShare
     }
     __syncthreads();
 
-    // Step 3: expansion, walking the candidates in visiting order.
+    // Step 3: expansion, walking the candidates in visiting order: one wave
+    // per bin (bins are independent), a 64-candidate block at a time, its
+    // lanes holding them (one thread per bin walking every candidate through
+    // LDS took 5 us for 124 candidates).
     const double fbase = sh.fbase;
-    for (int b = tid; b < nb; b += nthr) {
+    for (int b = wave; b < nb; b += nthr / kWave) {
         double load = sh.mload[b];
-        for (int r = 0; r < n_cand; ++r) {
-            if (sh.cbin[r] != b) continue;
-            const double c = (double)sh.ccost[r];
-            if (load + c <= fbase) {
-                sh.prom[sh.sorted[r]] = 1;
-                load += c;
+        for (int r0 = 0; r0 < n_cand; r0 += kWave) {
+            const int r = r0 + lane;
+            const bool in = r < n_cand && sh.cbin[r] == b;
+            const double c = in ? (double)sh.ccost[r] : 0.0;
+            unsigned long long todo = __ballot(in), taken = 0ull;
+            while (todo) {
+                const int l = __ffsll((long long)todo) - 1;
+                const double cl = readlane_d(c, l);
+                if (load + cl <= fbase) {
+                    taken |= 1ull << l;
+                    load += cl;
+                }
+                todo &= todo - 1ull;
             }
+            if ((taken >> lane) & 1ull) sh.prom[sh.sorted[r]] = 1;
         }
-        if (p.bin_loads) p.bin_loads[2 * nb + b] = load;
+        if (p.bin_loads && lane == 0) p.bin_loads[2 * nb + b] = load;
     }
     __syncthreads();
 }
@@ -584,8 +784,11 @@ __device__ void prune_all(const RouteParams& p, int tid, int nthr, PruneShared& 
     const int T = p.T, E = p.E, k = p.k, nb = p.n_bins;
 
     for (int e = tid; e < E; e += nthr) {
-        s_imp[e] = 0ull;
-        s_act[e] = s_must[e] = s_prom[e] = 0;
+        const int f = p.pair_stats ? p.trans[e] : 0;
+        s_imp[e] = p.pair_stats ? (unsigned long long)__double_as_longlong(p.imp_sum[e]) : 0ull;
+        s_act[e] = (f & kStatAct) != 0;
+        s_must[e] = (f & kStatMust) != 0;
+        s_prom[e] = 0;
         s_cost[e] = p.cost[e];
         const int b = p.bin ? p.bin[e] : 0;
         s_bin[e] = (b >= 0 && b < nb) ? b : -1;   // out-of-range bins (a precondition violation) count nowhere
@@ -599,10 +802,12 @@ __device__ void prune_all(const RouteParams& p, int tid, int nthr, PruneShared& 
     __syncthreads();
 
     // Step 1: A_act, importance, A_must (pairs mandatory on their own, and
-    // for the SUM rule every expert whose summed weight reaches tau).
-    // Batches of 8 pairs per thread: their loads are issued together.
+    // for the SUM rule every expert whose summed weight reaches tau): from
+    // k_expert_stats, or from the pairs here, in batches of 8 per thread,
+    // whose loads are issued together.
     constexpr int kB = 8;
-    for (int i0 = tid; i0 < T * k; i0 += kB * nthr) {
+    const int pairs = p.pair_stats ? 0 : T * k;
+    for (int i0 = tid; i0 < pairs; i0 += kB * nthr) {
         int ev[kB];
         double gv[kB];
         uint8_t mv[kB];
@@ -638,9 +843,10 @@ __device__ void prune_all(const RouteParams& p, int tid, int nthr, PruneShared& 
     // Then Sec. IV-C's final top-k would have nothing to choose from: steps
     // 2-3 run again with every token's own top expert mandatory (the only
     // departure from step 1 as written).
-    bool member = false;
+    // (Without candidates A_must is A_act, which no batch leaves empty.)
+    bool member = s_ncand == 0;
     for (int e = tid; e < E; e += nthr) member |= (s_must[e] | s_prom[e]) != 0;
-    if (!__syncthreads_or(member)) {   // (nothing was promoted either: s_prom stays zero)
+    if (s_ncand > 0 && !__syncthreads_or(member)) {   // (nothing was promoted either: s_prom stays zero)
         for (int t = tid; t < T; t += nthr) s_must[p.top1[t]] = 1;
         for (int b = tid; b < nb; b += nthr) s_aload[b] = s_mload[b] = 0.0;
         if (tid == 0) {
@@ -682,6 +888,7 @@ __device__ void prune_all(const RouteParams& p, int tid, int nthr, PruneShared& 
         }
     }
     __syncthreads();
+    if (tid < 2) p.counts[tid] = 0;   // compensation adds to these
     if (p.stats && tid == 0) {
         p.stats[0] = sh.stat[0];   // |A_act|
         p.stats[1] = sh.stat[1];   // |A_must|
@@ -857,7 +1064,6 @@ __device__ void place_shared(const RouteParams& p, const int* s_off, int tid, in
 // ascending within a slot, plus the FFN work lists, for batches of at most
 // kMaskT tokens: one workgroup; each expert's tokens are a bitmask in LDS and
 // every (token, slot) entry finds its row independently by counting set bits.
-// Also reports the refill/empty-slot counts of the compensation kernel.
 struct PermShared {
     int cnt[kMaxE + kMaxShared];
     int off[kMaxE + kMaxShared + 1];
@@ -869,11 +1075,6 @@ __device__ void permute_small(const RouteParams& p, int tid, int nthr, PermShare
     int* s_cnt = sh.cnt;
     int* s_off = sh.off;
     unsigned long long* s_mask = sh.mask;
-    if (tid == 0 && p.stats) {
-        p.stats[6] = p.counters[1];
-        p.stats[7] = p.counters[2];
-    }
-    if (!p.do_permute) return;
     const int T = p.T, E = p.E;
     const int W = (T + 63) / 64;
     fill_masks(p, 0, T, W, tid, nthr, s_mask, sh.pre);
@@ -921,10 +1122,6 @@ __global__ __launch_bounds__(kRouteThreads) void k_permute_scan(RouteParams p) {
     __shared__ int s_off[kMaxE + kMaxShared + 1];
     const int tid = threadIdx.x, E = p.E;
     const int nblk = (p.T + kMaskT - 1) / kMaskT;
-    if (tid == 0 && p.stats) {
-        p.stats[6] = p.counters[1];
-        p.stats[7] = p.counters[2];
-    }
     for (int x = tid; x < E + p.n_shared; x += kRouteThreads) {
         int c = p.T;
         if (x < E) {
@@ -959,7 +1156,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_permute_place(RouteParams p) 
 }
 
 hipError_t launch_permutation(const RouteParams& p, hipStream_t s) {
-    if (!p.do_permute || p.T <= kMaskT) {
+    if (p.T <= kMaskT) {
         hipLaunchKernelGGL(k_permute, dim3(1), dim3(kRouteThreads), 0, s, p);
         return hipGetLastError();
     }
@@ -994,8 +1191,8 @@ __global__ __launch_bounds__(kTokThreads) void k_compensate(RouteParams p) {
     // words serialise in the L2).
     __syncthreads();
     if (tid == 0) {
-        if (s_cnt[0]) atomicAdd(&p.counters[1], s_cnt[0]);
-        if (s_cnt[1]) atomicAdd(&p.counters[2], s_cnt[1]);
+        if (s_cnt[0]) atomicAdd(&p.counts[0], s_cnt[0]);
+        if (s_cnt[1]) atomicAdd(&p.counts[1], s_cnt[1]);
     }
 }
 
@@ -1014,13 +1211,14 @@ __device__ void route_fused_body(const RouteParams& p) {
     __shared__ int s_ids[kFusedWaves][kMaxK];
     __shared__ PruneShared sp;
     __shared__ PermShared sq;
-    __shared__ int32_t l_orig[kFusedT * kMaxK], l_top1[kFusedT], l_fin[kFusedT * kMaxK], l_ctr[4];
+    __shared__ int32_t l_orig[kFusedT * kMaxK], l_top1[kFusedT], l_fin[kFusedT * kMaxK];
     __shared__ double l_g[kFusedT * kMaxK], l_isum[kMaxE];
     __shared__ float l_w[kFusedT * kMaxK], l_cost[kMaxE];
     __shared__ int32_t l_bin[kMaxE];
     __shared__ uint8_t l_mflag[kFusedT * kMaxK], l_trans[kMaxE];
     __shared__ uint32_t l_masks[4 * (kMaxE / 32)];
     __shared__ int32_t l_stats[kStats];
+    int32_t* const l_counts = l_stats + 6;
     __shared__ double l_bl[3 * kMaxE];
     __shared__ double l_s[kFusedT * kMaxK];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -1035,7 +1233,7 @@ __device__ void route_fused_body(const RouteParams& p) {
     q.trans = l_trans;
     q.topk_ids = l_fin;
     q.topk_w = l_w;
-    q.counters = l_ctr;
+    q.counts = l_counts;
     q.imp_sum = l_isum;
     q.masks = p.masks ? l_masks : nullptr;
     q.stats = p.stats ? l_stats : nullptr;
@@ -1046,7 +1244,6 @@ __device__ void route_fused_body(const RouteParams& p) {
         l_cost[e] = p.cost[e];
         if (p.bin) l_bin[e] = p.bin[e];
     }
-    if (tid < 4) l_ctr[tid] = 0;
     for (int t = wave; t < p.T; t += kFusedWaves)
         route_token<EPL>(q, t, lane, q.orig_ids + (size_t)t * k, q.gbuf + (size_t)t * k, q.top1 + t,
                          q.mflag + (size_t)t * k);
@@ -1060,16 +1257,25 @@ __device__ void route_fused_body(const RouteParams& p) {
     __shared__ int s_cnt[2];
     if (tid < 2) s_cnt[tid] = 0;
     __syncthreads();
-    for (int t = wave; t < p.T; t += kFusedWaves)
-        compensate_token<EPL>(q, t, lane, q.orig_ids + (size_t)t * k, l_trans, s_ids[wave], s_sbuf[wave],
-                              &s_cnt[0], &s_cnt[1]);
-    __syncthreads();
-    if (tid == 0) {   // the only workgroup: the call's totals
-        l_ctr[1] = s_cnt[0];
-        l_ctr[2] = s_cnt[1];
+    if (sp.stat[3] == 0 && p.refill != CAEE_REFILL_LITERAL) {
+        // Nothing was pruned: every token keeps its list, one thread per slot
+        // with compensate_token's arithmetic.
+        for (int i = tid; i < p.T * k; i += kRouteThreads) {
+            const int t0 = i / k * k;
+            double total = 0.0;
+            for (int r = 0; r < k; ++r) total += l_s[t0 + r];
+            l_fin[i] = l_orig[i];
+            l_w[i] = (float)(p.rs * (l_s[i] / total));
+        }
+    } else {
+        for (int t = wave; t < p.T; t += kFusedWaves)
+            compensate_token<EPL>(q, t, lane, q.orig_ids + (size_t)t * k, l_trans, s_ids[wave], s_sbuf[wave],
+                                  &s_cnt[0], &s_cnt[1]);
     }
     __syncthreads();
-    if (p.do_permute || p.stats) permute_small(q, tid, kRouteThreads, sq);
+    if (tid < 2) l_counts[tid] = s_cnt[tid];   // the only workgroup: the call's totals
+    __syncthreads();
+    if (p.do_permute) permute_small(q, tid, kRouteThreads, sq);
     // Results read after this kernel: K_t, K_final and its weights, A_trans.
     for (int i = tid; i < p.T * k; i += kRouteThreads) {
         p.orig_ids[i] = l_orig[i];
@@ -1077,7 +1283,6 @@ __device__ void route_fused_body(const RouteParams& p) {
         p.topk_w[i] = l_w[i];
     }
     for (int e = tid; e < E; e += kRouteThreads) p.trans[e] = l_trans[e];
-    if (tid < 4) p.counters[tid] = l_ctr[tid];
     const int words = (E + 31) / 32;
     if (p.masks)
         for (int i = tid; i < 4 * words; i += kRouteThreads) p.masks[i] = l_masks[i];
@@ -1182,19 +1387,20 @@ hipError_t launch_route(const RouteParams& p, hipStream_t s) {
         hipLaunchKernelGGL(route_k, tok_grid, dim3(kTokThreads), 0, s, p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (p.rule == CAEE_IMPORTANCE_SUM) {
-            hipLaunchKernelGGL(k_importance_sum, dim3((p.E + kTokWaves - 1) / kTokWaves), dim3(kTokThreads), 0, s, p);
+        RouteParams q = p;
+        q.pair_stats = p.rule == CAEE_IMPORTANCE_SUM || (long long)p.T * p.k >= CAEE_PAIR_STATS;
+        if (q.pair_stats) {
+            hipLaunchKernelGGL(k_expert_stats, dim3(p.E), dim3(kStatWaves * kWave), 0, s, p);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k_prune, dim3(1), dim3(kRouteThreads), 0, s, p);
+        hipLaunchKernelGGL(k_prune, dim3(1), dim3(kRouteThreads), 0, s, q);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(comp_k, tok_grid, dim3(kTokThreads), 0, s, p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (!p.do_permute && !p.stats) return hipSuccess;
-        return launch_permutation(p, s);
+        return p.do_permute ? launch_permutation(p, s) : hipSuccess;
     };
     switch (p.epl) {
         case 1: return token_kernels(k_route_tokens<1>, k_compensate<1>, k_route_fused<1>);
@@ -1205,9 +1411,7 @@ hipError_t launch_route(const RouteParams& p, hipStream_t s) {
 }
 
 hipError_t launch_permute(const RouteParams& p, hipStream_t s) {
-    RouteParams q = p;
-    q.stats = nullptr;   // counters are not filled when routing did not run
-    return launch_permutation(q, s);
+    return launch_permutation(p, s);
 }
 
 }  // namespace caee
