@@ -276,7 +276,8 @@ caee_status_t caee_quantize_rows(int32_t src_dtype, const void* src, int64_t row
  *      pruning and compensation with it on `stream` -- so pruning keeps the
  *      mandatory experts, promotes the resident candidates, and prunes the
  *      candidates that would have to be fetched;
- *   2. waits on the host for that routing step to finish (the only host
+ *   2. enqueues the FFN of the experts resident by then and of the shared
+ *      ones, waits on the host for the routing step to finish (the only host
  *      synchronisation of the call) and reads A_trans;
  *   3. plans the call (caee_lru_step): experts of A_trans already resident
  *      are hits; the others are misses and go, in ascending expert order,

@@ -339,6 +339,7 @@ struct RouteParams {
     double* gbuf;
     int32_t* top1;
     uint8_t* trans;
+    uint8_t* trans_host;   // a second copy of A_trans, in page-locked host memory (NULL: none)
     uint8_t* mflag;
     double* imp_sum;
     int32_t* counts;    // refilled and empty slots (stats[6], stats[7] when there are stats)

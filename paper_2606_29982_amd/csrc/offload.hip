@@ -5,10 +5,13 @@
 // already on the device compute while the missing ones are still being
 // copied over the host link.
 //
-// Per call:  cost table from residency (Sec. IV-A: R = 0 for a resident
-// expert) -> routing/pruning/compensation on `stream` -> host reads A_trans
-// -> LRU plan -> H2D copies in batches on `copy_stream` -> FFN pass of the
-// hits, then one pass per batch as it lands -> combine.
+// Per call:  cost, address and pass tables from residency (Sec. IV-A: R = 0
+// for a resident expert), uploaded when they differ from the last ones ->
+// routing/pruning/compensation on `stream`, whose kernel leaves A_trans in
+// page-locked host memory -> FFN pass of the experts resident by now, launched
+// without waiting -> host reads A_trans once routing is done -> LRU plan ->
+// H2D copies in batches on `copy_stream`, one FFN pass per batch as it lands
+// -> combine.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -34,12 +37,17 @@ struct caee_offload {
     std::vector<int64_t> slot_used;
     int64_t call = 0;
     caee_offload_stats_t st{};
-    // per-call tables: device block and its page-locked host mirror
+    // per-call tables: device block, and page-locked host buffers it is
+    // uploaded from (one for the tables a call starts with, one for those
+    // with its misses: see upload())
     //   cost [E] fp32 | wtab [2 (E + n_shared)] pointers | pass_of [E + n_shared] int32
     char* dev_tab = nullptr;
     char* host_tab = nullptr;
     size_t off_wtab = 0, off_pass = 0, tab_bytes = 0;
-    uint8_t* host_trans = nullptr;           // [E] A_trans flags read back after routing
+    std::vector<char> tab, tab_now;          // the tables being built; what dev_tab holds (in stream order)
+    bool tab_valid = false;                  // whether tab_now is known
+    uint8_t* host_trans = nullptr;           // [E] A_trans flags, written by the routing kernel
+    uint8_t* dev_trans = nullptr;            // its address on the device
     hipEvent_t ev_route = nullptr, ev_done = nullptr;
     bool have_done = false;
     std::vector<hipEvent_t> ev_fetch, ev_pass;
@@ -235,15 +243,20 @@ caee_status_t caee_offload_create(const caee_layer_desc_t* desc, const caee_offl
     h->off_pass = h->off_wtab + align256_((size_t)2 * X * sizeof(void*));
     h->tab_bytes = h->off_pass + align256_((size_t)X * 4);
     hipError_t e1 = hipMalloc((void**)&h->dev_tab, h->tab_bytes);
-    hipError_t e2 = e1 == hipSuccess ? hipHostMalloc((void**)&h->host_tab, h->tab_bytes, hipHostMallocDefault) : e1;
-    hipError_t e3 = e2 == hipSuccess ? hipHostMalloc((void**)&h->host_trans, align256_(d0.E), hipHostMallocDefault) : e2;
+    hipError_t e2 = e1 == hipSuccess ? hipHostMalloc((void**)&h->host_tab, 2 * h->tab_bytes, hipHostMallocDefault) : e1;
+    // Coherent: the routing kernel's stores reach it without a copy.
+    hipError_t e3 = e2 == hipSuccess ? hipHostMalloc((void**)&h->host_trans, align256_(d0.E),
+                                                     hipHostMallocMapped | hipHostMallocCoherent) : e2;
+    if (e3 == hipSuccess) e3 = hipHostGetDevicePointer((void**)&h->dev_trans, h->host_trans, 0);
     hipError_t e4 = e3 == hipSuccess ? hipEventCreateWithFlags(&h->ev_route, hipEventDisableTiming) : e3;
     hipError_t e5 = e4 == hipSuccess ? hipEventCreateWithFlags(&h->ev_done, hipEventDisableTiming) : e4;
     if (e5 != hipSuccess) {
         release(h);
         return hip_fail(e5, "offload allocation");
     }
-    std::memset(h->host_tab, 0, h->tab_bytes);
+    std::memset(h->host_tab, 0, 2 * h->tab_bytes);
+    h->tab.assign(h->tab_bytes, 0);
+    h->tab_now.assign(h->tab_bytes, 0);
     *handle = h;
     return CAEE_OK;
 }
@@ -301,18 +314,50 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipStream_t cs = reinterpret_cast<hipStream_t>(copy_stream);
     char* wsb = (char*)ws;
-    const int E = d.E, X = d.E + d.n_shared;
+    const int E = d.E;
 
     // Tables and slots are rewritten below; the previous call must be done with them.
     if (h->have_done) HIP_TRY(hipStreamWaitEvent(s, h->ev_done, 0), "hipStreamWaitEvent");
-    // 1. cost table from residency, then routing with one bin.
-    float* hcost = (float*)h->host_tab;
-    for (int e = 0; e < E; ++e) hcost[e] = h->slot_of[e] >= 0 ? 0.0f : h->miss_cost;
-    HIP_TRY(hipMemcpyAsync(h->dev_tab, hcost, (size_t)E * 4, hipMemcpyHostToDevice, s), "cost table copy");
+    // 1. tables from residency: costs, and for the first FFN pass the
+    // addresses of every resident expert (one that the call does not need has
+    // no rows); an absent one is in no pass yet.
+    float* cost = (float*)h->tab.data();
+    const void** wtab = (const void**)(h->tab.data() + h->off_wtab);
+    int32_t* pass_of = (int32_t*)(h->tab.data() + h->off_pass);
+    for (int e = 0; e < E; ++e) {
+        const bool in = h->slot_of[e] >= 0;
+        const size_t sl = in ? h->slot_of[e] : 0;
+        cost[e] = in ? 0.0f : h->miss_cost;
+        wtab[2 * e] = h->slot_w13 + sl * h->w13_bytes;
+        wtab[2 * e + 1] = h->slot_w2 + sl * h->w2_bytes;
+        pass_of[e] = in ? 0 : -1;
+    }
+    for (int sx = 0; sx < d.n_shared; ++sx) {
+        wtab[2 * (E + sx)] = h->sh_w13 + (size_t)sx * h->w13_bytes;
+        wtab[2 * (E + sx) + 1] = h->sh_w2 + (size_t)sx * h->w2_bytes;
+        pass_of[E + sx] = 0;
+    }
+    // Uploads the tables if dev_tab does not hold them already, from host
+    // buffer 0 before routing or 1 after it.  The copy from buffer 0 of the
+    // call before is done (its host waited for its routing, which follows
+    // that copy), and so is the one from buffer 1 once this call's routing
+    // is (`s` is behind ev_done).
+    auto upload = [&](int buf) -> caee_status_t {
+        if (h->tab_valid && h->tab == h->tab_now) return CAEE_OK;
+        char* from = h->host_tab + buf * h->tab_bytes;
+        std::memcpy(from, h->tab.data(), h->tab_bytes);
+        h->tab_valid = false;
+        HIP_TRY(hipMemcpyAsync(h->dev_tab, from, h->tab_bytes, hipMemcpyHostToDevice, s), "table copy");
+        h->tab_now = h->tab;
+        h->tab_valid = true;
+        return CAEE_OK;
+    };
+    CAEE_TRY(upload(0));
     RouteParams rp = make_route_params(desc, logits, bias, (const float*)h->dev_tab, nullptr, wsb, L);
     rp.chunk_small = call_chunk_small(d, h->layout == CAEE_LAYOUT_TILED);
     rp.chunk_big = call_chunk_big(d, h->layout == CAEE_LAYOUT_TILED);
     set_route_outputs(rp, out, wsb, L);
+    rp.trans_host = h->dev_trans;
     FfnParams fp = make_ffn_params(desc, x, rp.topk_ids, rp.topk_w, nullptr, y, wsb, L);
     fp.sh_w13 = h->sh_w13;
     fp.sh_w2 = h->sh_w2;
@@ -322,20 +367,24 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
     fp.pass_id = 0;
     FfnCall fc;
     CAEE_TRY(ffn_begin(desc, fp, L, s, &fc));
-    // Any return below must first bring the side stream back into `stream`.
+    // A return below leaves work behind that reads the tables and slots: the
+    // next call waits for it.
     auto joined = [&](caee_status_t st) {
-        if (fc.side != fc.main && hipEventRecord(fc.ev_join, fc.side) == hipSuccess)
-            (void)hipStreamWaitEvent(fc.main, fc.ev_join, 0);
+        if (hipEventRecord(h->ev_done, s) == hipSuccess) h->have_done = true;
         return st;
     };
     fc.shared_done = route_runs_shared(d);   // as caee_moe_layer, so both give the same bits
     caee_status_t st = run_route_layer(desc, rp, out, wsb, L, s, fc.shared_done ? &fp : nullptr);
     if (st != CAEE_OK) return joined(st);
-    // 2. read A_trans back.
-    hipError_t he = hipMemcpyAsync(h->host_trans, wsb + L.trans, E, hipMemcpyDeviceToHost, s);
-    if (he == hipSuccess) he = hipEventRecord(h->ev_route, s);
-    if (he == hipSuccess) he = hipEventSynchronize(h->ev_route);
-    if (he != hipSuccess) return joined(hip_fail(he, "A_trans read-back"));
+    hipError_t he = hipEventRecord(h->ev_route, s);
+    if (he != hipSuccess) return joined(hip_fail(he, "hipEventRecord"));
+    // The FFN of the resident and shared experts follows routing without
+    // waiting for the host.
+    st = ffn_routed(desc, fp, L, &fc, false);
+    if (st != CAEE_OK) return joined(st);
+    // 2. A_trans, once routing is done.
+    he = hipEventSynchronize(h->ev_route);
+    if (he != hipSuccess) return joined(hip_fail(he, "waiting for routing"));
 
     // 3. plan.
     std::vector<int32_t> fetch(E), fetch_slot(E);
@@ -358,32 +407,20 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
         return joined(st_);
     };
 
-    // Tables: weight addresses and the pass of every expert slot.
-    const void** wtab = (const void**)(h->host_tab + h->off_wtab);
-    int32_t* pass_of = (int32_t*)(h->host_tab + h->off_pass);
-    for (int e = 0; e < E; ++e) {
-        const int sl = h->slot_of[e] >= 0 && h->host_trans[e] ? h->slot_of[e] : 0;
-        wtab[2 * e] = h->slot_w13 + (size_t)sl * h->w13_bytes;
-        wtab[2 * e + 1] = h->slot_w2 + (size_t)sl * h->w2_bytes;
-        pass_of[e] = h->host_trans[e] ? 0 : -1;
-    }
+    // The misses' addresses and passes (the slots of experts they replace
+    // hold nothing this call needs).
     for (int i = 0; i < misses; ++i) {
         const int e = fetch[i], sl = fetch_slot[i];
         wtab[2 * e] = h->slot_w13 + (size_t)sl * h->w13_bytes;
         wtab[2 * e + 1] = h->slot_w2 + (size_t)sl * h->w2_bytes;
         pass_of[e] = 1 + i / batch;
     }
-    for (int sx = 0; sx < d.n_shared; ++sx) {
-        wtab[2 * (E + sx)] = h->sh_w13 + (size_t)sx * h->w13_bytes;
-        wtab[2 * (E + sx) + 1] = h->sh_w2 + (size_t)sx * h->w2_bytes;
-        pass_of[E + sx] = 0;
-    }
-    (void)X;
     if (ensure_events(h->ev_fetch, n_batches) != CAEE_OK || ensure_events(h->ev_pass, n_batches + 1) != CAEE_OK)
         return rollback(CAEE_ERR_HIP);
-    he = hipMemcpyAsync(h->dev_tab + h->off_wtab, h->host_tab + h->off_wtab, h->tab_bytes - h->off_wtab,
-                        hipMemcpyHostToDevice, s);
-    if (he != hipSuccess) return rollback(hip_fail(he, "table copy"));
+    if (misses > 0) {
+        st = upload(1);
+        if (st != CAEE_OK) return rollback(st);
+    }
 
     // 4. copies and FFN passes.  Slots overwritten here were last read by an
     // earlier call, which ended with ev_done.
@@ -391,8 +428,6 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
         he = hipStreamWaitEvent(cs, h->ev_done, 0);
         if (he != hipSuccess) return rollback(hip_fail(he, "hipStreamWaitEvent"));
     }
-    st = ffn_routed(desc, fp, L, &fc, false);
-    if (st != CAEE_OK) return rollback(st);
     const int cached = misses - staged;
     for (int b = 0; b < n_batches; ++b) {
         for (int i = b * batch; i < std::min(misses, (b + 1) * batch); ++i) {

@@ -860,7 +860,10 @@ __device__ void prune_all(const RouteParams& p, int tid, int nthr, PruneShared& 
 
     // Step 4: A_trans = A_must + promoted; masks and counters by ballot,
     // one 64-expert block per wave, counts added in LDS.
-    for (int e = tid; e < E; e += nthr) p.trans[e] = s_must[e] | s_prom[e];
+    for (int e = tid; e < E; e += nthr) {
+        p.trans[e] = s_must[e] | s_prom[e];
+        if (p.trans_host) p.trans_host[e] = s_must[e] | s_prom[e];
+    }
     const int words = (E + 31) / 32;
     for (int base = wave * kWave; base < E; base += nthr) {
         const int e = base + lane;
