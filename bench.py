@@ -41,7 +41,7 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_2606_29982_amd", "csrc", n)
 # these sources.
 MFMA_FILE = os.path.join(ROOT, "profiles", "prefill8_deepseek_r1_t4096_mfma.json")
 PREFILL_SOURCES = [os.path.join(ROOT, "paper_2606_29982_amd", "csrc", n)
-                   for n in ("ffn_prefill8.hip", "fp8_codec.h", "caee_internal.h")]
+                   for n in ("ffn_prefill8.h", "fp8_codec.h", "caee_internal.h")]
 
 
 def kernel_sources_sha256(paths=None):

@@ -47,12 +47,6 @@ constexpr int kPrefillT = CAEE_PREFILL_T;
 constexpr int kGemmT = CAEE_GEMM_T;
 // Row-major 8-bit batches above this many tokens take 128-row staged chunks.
 constexpr int kStagedWideT = 256;
-// bf16 big chunks (experts with more rows than a small chunk holds) run
-// the same LDS-pipelined GEMM, as wide as its token tile (0 disables).
-#ifndef CAEE_GEMM_BF16
-#define CAEE_GEMM_BF16 1
-#endif
-constexpr int kGemmBf16 = CAEE_GEMM_BF16;
 // FFN kernel launch (one place to change how the FFN kernels are enqueued).
 template <typename K, typename... Args>
 inline void ffn_launch(K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args) {
@@ -67,6 +61,8 @@ inline void ffn_launch(K kernel, dim3 grid, dim3 block, hipStream_t s, Args... a
 // The grid follows the chunks the batch can have (T = 1: 9, not 257): empty
 // workgroups cost about 0.2 us per thousand.
 constexpr int kSmallGridPerCu = 64;
+constexpr int kXcds = 8;            // accelerator complex dies, each with its own L2
+constexpr int kEvenShares = 2;      // n_chunks[2]: whether every eighth big chunk makes an even share (see below)
 constexpr int kFfnThreads = 256;    // 4 independent waves per FFN workgroup
 #ifndef CAEE_ROUTE_SHARED
 #define CAEE_ROUTE_SHARED 1   // batches of up to 16 tokens run the shared experts' gate/up in the routing launch
@@ -140,8 +136,8 @@ struct WsLayout {
     size_t perm_tok;            // [P] token of each permuted row
     size_t perm_pos;            // [T][k + n_shared] permuted row of each (token, slot), -1 unused
     size_t perm_blk;            // [ceil(T / kMaskT)][E] per token block: expert counts, then first rows
-    size_t chunks;              // [max_chunks][4] (expert slot, first row, rows, pair): small chunks, then big
-    size_t n_chunks;            // [2] small and big chunk counts
+    size_t chunks;              // [max_chunks][4] (expert slot, first row, rows, one of several): small chunks, then big
+    size_t n_chunks;            // [3] small and big chunk counts, and kEvenShares
     size_t h;                   // [P][f] SwiGLU activations (weight dtype; fp32 for fp8)
     size_t y;                   // [P][d] expert outputs (fp32; bf16 on the 8-bit path)
     size_t xq, xs;              // fp8 path: [T][d] e4m3 codes of x and [T][d/128] fp32 scales
@@ -222,7 +218,7 @@ inline int big_token_blocks(const caee_layer_desc_t& d) {
 #define CAEE_ALL_BIG_FP8 8
 #endif
 #ifndef CAEE_ALL_BIG_BF16
-#define CAEE_ALL_BIG_BF16 16
+#define CAEE_ALL_BIG_BF16 14
 #endif
 constexpr int kAllBigRowsFp8 = CAEE_ALL_BIG_FP8, kAllBigRowsBf16 = CAEE_ALL_BIG_BF16;   // see call_chunk_small
 bool gemm_fp8_applies(const caee_layer_desc_t& d, bool tiled);
@@ -251,7 +247,8 @@ inline int call_big_blocks(const caee_layer_desc_t& d, bool tiled) {
 //   8-bit: T = 200 (6.25 rows) 1914 us with small chunks, 1923 without;
 //          T = 400 (12.5) 2299 / 2024; T = 600 (18.8) 2810 / 2051;
 //          T = 1000 (31) 2754 / 2189; T = 2500 equal;
-//   bf16:  T = 300 (9.4) 3583 / 3918; T = 800 (25) 4643 / 4065; T = 2048 equal.
+//   bf16:  T = 300 (9.4) 3589 / 3688; T = 400 (12.5) 3613 / 3684; T = 500
+//          (15.6) 4020 / 3767; T = 800 (25) 4643 / 4065.
 inline int call_chunk_small(const caee_layer_desc_t& d, bool tiled) {
     const int nb = big_token_blocks(d);
     const long long pairs = (long long)d.T * d.k;
@@ -403,10 +400,24 @@ struct FfnParams {
 // listed first, then the big ones).
 struct ChunkRef {
     int xs, row0, ntok;
-    int pair;   // list offset (+1 / -1) of the other piece of a pair, 0 if unpaired
+    int multi;  // the expert's rows are cut into several chunks: its weights are read again
 };
 
 __device__ inline int ffn_list_size(const FfnParams& p) { return p.n_chunks[p.list]; }
+
+// Order of the big chunks' items.  Workgroups go to the XCDs round robin
+// (workgroup b to XCD b % 8).  By XCD: XCD x takes the chunks x, x + 8, ...,
+// all items of each, so that the items that read a chunk's token rows share an
+// L2; worth it while a chunk has many items and the XCDs' shares are even (a
+// few popular experts make them differ by whole chunks).  Measured by XCD / in
+// plain order, R1-shaped layer: bf16 T = 2048 4228 / 4319 us, 8-bit T = 4096
+// 2819 / 2881; skewed bf16 T = 1000 2679 / 2523, skewed 8-bit T = 128 554 / 527,
+// 8-bit T = 600 2038 / 2009; d = 2048, f = 1408 (8 down items per chunk), down
+// of T = 1500: 186 / 151.
+constexpr int kXcdMinItems = 16;
+__device__ inline bool items_by_xcd(const FfnParams& p, int items_per_chunk) {
+    return items_per_chunk >= kXcdMinItems && gridDim.x % kXcds == 0 && p.n_chunks[kEvenShares];
+}
 
 __device__ inline ChunkRef ffn_chunk(const FfnParams& p, int c) {
     const int32_t* ch = p.chunks + 4 * ((p.list ? p.n_chunks[0] : 0) + c);
@@ -480,6 +491,7 @@ bool gemm_fp8_supports(const FfnParams& p, int nb);
 bool gemm_bf16_supports(const FfnParams& p, int nb);
 hipError_t launch_gemm(const FfnParams& p, bool gate_up, int max_chunks, hipStream_t s);   // bf16 big chunks
 hipError_t launch_prefill8(const FfnParams& p, bool gate_up, int max_chunks, hipStream_t s);
+hipError_t launch_prefill8_down(const FfnParams& p, unsigned workgroups, hipStream_t s);
 hipError_t launch_down_fp8(const FfnParams& p, int nb, int max_chunks, hipStream_t s);
 hipError_t launch_pack(const void* src, void* dst, long long rows, long long row_units, long long count,
                        hipStream_t s);

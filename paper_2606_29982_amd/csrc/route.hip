@@ -914,8 +914,11 @@ __global__ __launch_bounds__(kRouteThreads) void k_prune(RouteParams p) {
 // (shared expert s owns rows s*T .. s*T + T - 1, known before routing), then
 // the routed ones in expert order.  Then one small chunk per slot with at
 // most chunk_small rows, and ceil(rows / chunk_big) near-equal big chunks per
-// larger slot, the small chunks listed first.
-__device__ void build_lists(const RouteParams& p, const int* s_cnt, int* s_off, int tid) {
+// larger slot, the small chunks listed first.  s_work collects the big
+// chunks' work (16-token tiles, and two for what an item costs at any width)
+// by list position modulo 8; publish_balance, after a barrier, tells the FFN
+// whether those shares are within 5 % of even.
+__device__ void build_lists(const RouteParams& p, const int* s_cnt, int* s_off, int* s_work, int tid) {
     // Run by the first four waves of the workgroup (every thread calls it:
     // it holds a barrier).  Lane gl of the 256 takes slots [gl*per, gl*per+per)
     // in row order, so the scans below follow the slots' row order.
@@ -925,6 +928,7 @@ __device__ void build_lists(const RouteParams& p, const int* s_cnt, int* s_off, 
     const int cs = p.chunk_small, cb = p.chunk_big;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const bool active = wave < kW;   // uniform per wave
+    if (tid < kXcds) s_work[tid] = 0;
     const int per = (nx + kW * kWave - 1) / (kW * kWave);
     const int gl = wave * kWave + lane;
     const int lo = gl * per;
@@ -980,9 +984,8 @@ __device__ void build_lists(const RouteParams& p, const int* s_cnt, int* s_off, 
                 chk[0] = x;
                 chk[1] = run + c * size;
                 chk[2] = min(size, cnt - c * size);
-                // Pieces 2i and 2i + 1 form a pair (rows adjacent, at most
-                // 2 * chunk_big together); a last odd piece has none.
-                chk[3] = (c & 1) ? -1 : (c + 1 < pieces ? 1 : 0);
+                chk[3] = pieces > 1;
+                atomicAdd(&s_work[(brun + c - stotal) % kXcds], (chk[2] + 15) / 16 + 2);
             }
             brun += pieces;
         }
@@ -994,6 +997,16 @@ __device__ void build_lists(const RouteParams& p, const int* s_cnt, int* s_off, 
         p.n_chunks[0] = stotal;
         p.n_chunks[1] = btotal;
     }
+}
+
+__device__ inline void publish_balance(const RouteParams& p, const int* s_work, int tid) {
+    if (tid != 0 || p.T <= 32) return;   // no big chunks up to 32 tokens
+    int most = 0, total = 0;
+    for (int i = 0; i < kXcds; ++i) {
+        most = max(most, s_work[i]);
+        total += s_work[i];
+    }
+    p.n_chunks[kEvenShares] = (long long)most * kXcds * 20 <= (long long)total * 21;
 }
 
 // Token-block bitmasks: bit (t - t0) of word (x, (t - t0) / 64) is set when
@@ -1070,6 +1083,7 @@ __device__ void place_shared(const RouteParams& p, const int* s_off, int tid, in
 struct PermShared {
     int cnt[kMaxE + kMaxShared];
     int off[kMaxE + kMaxShared + 1];
+    int work[kXcds];
     unsigned long long mask[kMaxE * (kMaskT / 64)];
     int pre[kMaxE * (kMaskT / 64)];
 };
@@ -1090,8 +1104,9 @@ __device__ void permute_small(const RouteParams& p, int tid, int nthr, PermShare
         s_cnt[x] = c;
     }
     __syncthreads();
-    build_lists(p, s_cnt, s_off, tid);
+    build_lists(p, s_cnt, s_off, sh.work, tid);
     __syncthreads();
+    publish_balance(p, sh.work, tid);
     place_shared(p, s_off, tid, nthr);
     place_entries(p, 0, T, W, s_off, tid, nthr, s_mask, sh.pre);
 }
@@ -1123,6 +1138,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_permute_count(RouteParams p) 
 __global__ __launch_bounds__(kRouteThreads) void k_permute_scan(RouteParams p) {
     __shared__ int s_cnt[kMaxE + kMaxShared];
     __shared__ int s_off[kMaxE + kMaxShared + 1];
+    __shared__ int s_work[kXcds];
     const int tid = threadIdx.x, E = p.E;
     const int nblk = (p.T + kMaskT - 1) / kMaskT;
     for (int x = tid; x < E + p.n_shared; x += kRouteThreads) {
@@ -1134,8 +1150,9 @@ __global__ __launch_bounds__(kRouteThreads) void k_permute_scan(RouteParams p) {
         s_cnt[x] = c;
     }
     __syncthreads();
-    build_lists(p, s_cnt, s_off, tid);
+    build_lists(p, s_cnt, s_off, s_work, tid);
     __syncthreads();
+    publish_balance(p, s_work, tid);
     for (int x = tid; x < E; x += kRouteThreads) {
         int run = s_off[x];
         for (int b = 0; b < nblk; ++b) {

@@ -50,10 +50,26 @@ def test_fp8_staged(shape, tiled, T):
 
 
 @pytest.mark.parametrize("tiled", [True, False])
-@pytest.mark.parametrize("T", [63, 64, 200])
+@pytest.mark.parametrize("T", [55, 56, 200])
 def test_bf16_rules(T, tiled):
-    # 16 experts, 4 per token: 16 rows per expert at 64 tokens
+    # 16 experts, 4 per token: 14 rows per expert at 56 tokens
     _case(BF16, T, tiled=tiled)
+
+
+# Contractions whose stage counts leave 1, 2 and 3 steps after the stage loop
+# (bf16: 64-element stages; 8-bit: 128), every token-tile count, experts in one
+# chunk and in several (whose weights take the cached loads), odd tile counts
+# among them; d = 384 goes to the staged kernels.
+@pytest.mark.parametrize("d,f", [(1280, 128), (256, 384), (512, 1408), (384, 256)])
+@pytest.mark.parametrize("T,zipf", [(100, None), (300, 1.1), (600, None), (777, 1.1)])
+def test_bf16_gemm(d, f, T, zipf):
+    _case(BF16.with_(name=f"bf16-{d}-{f}", d=d, f=f), T, zipf=zipf)
+
+
+@pytest.mark.parametrize("d,f", [(1280, 384), (768, 640), (256, 896)])
+@pytest.mark.parametrize("T,zipf", [(300, 1.1), (1300, None), (1500, 1.1)])
+def test_fp8_prefill_tails(d, f, T, zipf):
+    _case(FP8.with_(name=f"fp8-{d}-{f}", d=d, f=f), T, zipf=zipf)
 
 
 def test_noalloc_limit_of_decode_batches():
