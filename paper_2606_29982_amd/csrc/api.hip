@@ -300,12 +300,12 @@ caee_status_t down_list(const caee_layer_desc_t* d, FfnParams p, int list, int n
 }  // namespace
 
 caee_status_t ffn_begin(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, hipStream_t s,
-                        FfnCall* call) {
+                        FfnCall* call, bool x_done) {
     (void)L;
     *call = FfnCall{};
     call->main = s;
     call->side = s;
-    if (d->w_dtype == CAEE_FP8_E4M3)
+    if (d->w_dtype == CAEE_FP8_E4M3 && !x_done)
         CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, s, "quantise x",
                               [&] { return launch_quant_rows(p.x, 1, d->T, d->d, p.xq, p.xs, s); }));
     return CAEE_OK;
@@ -378,12 +378,12 @@ void set_route_outputs(RouteParams& p, const caee_route_out_t* out, char* ws, co
 }
 
 caee_status_t run_route_layer(const caee_layer_desc_t* d, RouteParams& p, const caee_route_out_t* out, char* ws,
-                              const WsLayout& L, hipStream_t s, const FfnParams* shared_fp) {
+                              const WsLayout& L, hipStream_t s, const FfnParams* shared_fp, bool shared) {
     set_route_outputs(p, out, ws, L);
     p.do_permute = 1;
     if (shared_fp)
         return timed_launch(CAEE_KERNEL_ROUTE, s, "route",
-                            [&] { return launch_route_shared(p, *shared_fp, d->w_dtype, s); });
+                            [&] { return launch_route_shared(p, *shared_fp, d->w_dtype, shared, s); });
     return timed_launch(CAEE_KERNEL_ROUTE, s, "route", [&] { return launch_route(p, s); });
 }
 
@@ -426,9 +426,10 @@ caee_status_t moe_layer_run(const caee_layer_desc_t* desc, const void* x, const 
     set_route_outputs(p, out, wsb, L);
     const FfnParams fp = make_ffn_params(desc, x, p.topk_ids, p.topk_w, weights, y, wsb, L);
     FfnCall call;
-    CAEE_TRY(ffn_begin(desc, fp, L, s, &call));
+    const bool x_done = route_quantises_x(*desc);
+    CAEE_TRY(ffn_begin(desc, fp, L, s, &call, x_done));
     call.shared_done = route_runs_shared(*desc);
-    CAEE_TRY(run_route_layer(desc, p, out, wsb, L, s, call.shared_done ? &fp : nullptr));
+    CAEE_TRY(run_route_layer(desc, p, out, wsb, L, s, call.shared_done || x_done ? &fp : nullptr, call.shared_done));
     CAEE_TRY(ffn_routed(desc, fp, L, &call, side));
     return ffn_end(fp, &call);
 }

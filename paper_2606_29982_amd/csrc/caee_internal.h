@@ -475,9 +475,11 @@ __device__ inline const float* ffn_scales(const FfnParams& p, int xs, bool w2, s
 hipError_t launch_route(const RouteParams& p, hipStream_t s);
 // Small batches: the single-workgroup routing launch also runs the shared
 // experts' gate/up (their rows hold every token and come first, so they
-// need nothing routing computes) in workgroups of its own.
+// need nothing routing computes) in workgroups of its own, and quantises x for
+// 8-bit weights.
 bool route_runs_shared(const caee_layer_desc_t& d);
-hipError_t launch_route_shared(const RouteParams& p, const FfnParams& fp, int w_dtype, hipStream_t s);
+bool route_quantises_x(const caee_layer_desc_t& d);
+hipError_t launch_route_shared(const RouteParams& p, const FfnParams& fp, int w_dtype, bool shared, hipStream_t s);
 hipError_t launch_permute(const RouteParams& p, hipStream_t s);
 hipError_t launch_gate_up(const FfnParams& p, int w_dtype, int nb, int max_chunks, hipStream_t s);
 hipError_t launch_down(const FfnParams& p, int w_dtype, int nb, int max_chunks, hipStream_t s);
@@ -514,11 +516,11 @@ FfnParams make_ffn_params(const caee_layer_desc_t* d, const void* x, const int32
 // Routing, pruning, compensation and permutation of a whole-layer call; the
 // routing results go to `out` when given, else to the workspace.
 caee_status_t run_route_layer(const caee_layer_desc_t* d, RouteParams& p, const caee_route_out_t* out, char* ws,
-                              const WsLayout& L, hipStream_t s, const FfnParams* shared_fp = nullptr);
+                              const WsLayout& L, hipStream_t s, const FfnParams* shared_fp = nullptr, bool shared = true);
 void set_route_outputs(RouteParams& p, const caee_route_out_t* out, char* ws, const WsLayout& L);
 
 // The FFN of one layer call, in three parts:
-//   ffn_begin   (fp8) quantises x;
+//   ffn_begin   (fp8) quantises x, unless the routing launch does (x_done);
 //   ffn_routed  after the permutation, runs the big chunks on the main
 //               stream and (two_streams) the small chunks on a side stream
 //               forked from it; with p.pass_of set only pass p.pass_id runs;
@@ -529,7 +531,7 @@ struct FfnCall {
     bool shared_done = false;   // the routing launch already ran the shared experts' gate/up
 };
 caee_status_t ffn_begin(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, hipStream_t s,
-                        FfnCall* call);
+                        FfnCall* call, bool x_done = false);
 caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, FfnCall* call,
                          bool two_streams);
 caee_status_t ffn_end(const FfnParams& p, FfnCall* call);

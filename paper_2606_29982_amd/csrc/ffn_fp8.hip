@@ -21,50 +21,11 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kScaleOne = 127;   // E8M0 exponent of 1.0 for the MFMA's own block scales
 
-// Quantisation of one block of 128 consecutive values by 16 lanes, lane l
-// holding values 8l .. 8l + 7: scale = amax / 448 (1 for an all-zero block),
-// code = e4m3(value / scale), all in fp32.  Returns the scale.
-__device__ inline float quant_block(const float (&v)[8], uint8_t* q, int l) {
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-    const float sc = amax > 0.0f ? amax / kE4M3Max : 1.0f;
-    uint2 c;
-    c.x = e4m3_code4(v[0] / sc, v[1] / sc, v[2] / sc, v[3] / sc);
-    c.y = e4m3_code4(v[4] / sc, v[5] / sc, v[6] / sc, v[7] / sc);
-    *(uint2*)(q + 8 * l) = c;
-    return sc;
-}
-
-__device__ inline void load8(const float* src, float (&v)[8]) {
-    const float4 a = *(const float4*)src, b = *(const float4*)(src + 4);
-    v[0] = a.x;
-    v[1] = a.y;
-    v[2] = a.z;
-    v[3] = a.w;
-    v[4] = b.x;
-    v[5] = b.y;
-    v[6] = b.z;
-    v[7] = b.w;
-}
-__device__ inline void load8(const uint16_t* src, float (&v)[8]) {   // bf16
-    const uint4 w = *(const uint4*)src;
-    const uint32_t p[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[2 * i] = __uint_as_float(p[i] << 16);
-        v[2 * i + 1] = __uint_as_float(p[i] & 0xFFFF0000u);
-    }
-}
-
 // All blocks of `rows` consecutive rows, 16 lanes per block (one or two
 // 16-byte loads, an 8-byte store of codes and four cross-lane steps).  Bound
 // by memory traffic at prefill sizes: 4096 bf16 rows of 7168 17.6 us (5.0
 // TB/s); one wavefront per block, two values a lane: 43.1 us.  Two or four
 // blocks per lane group: 18.1, 20.8 us.
-constexpr int kQuantLanes = 16;
 __global__ __launch_bounds__(256) void k_quant_rows(const void* src, int src_bf16, long long rows, int cols,
                                                     uint8_t* q, float* scale) {
     const long long b = ((long long)blockIdx.x * 256 + threadIdx.x) / kQuantLanes;   // in memory order
@@ -103,11 +64,87 @@ __device__ inline i32x8_t join(const u32x4_t& lo, const u32x4_t& hi) {
     return i32x8_t{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
 }
 
+// Loads through global-address-space pointers compile to global_load
+// (a flat_load would also count against the LDS wait counter).
+typedef const __attribute__((address_space(1))) u32x4_t g_u32x4_t;
+__device__ inline u32x4_t load_stream(const u32x4_t* p) { return __builtin_nontemporal_load((g_u32x4_t*)p); }
+__device__ inline u32x4_t load_cached(const u32x4_t* p) { return *(g_u32x4_t*)p; }
+
 // Contraction of one 16-row tile against up to NB 16-token blocks over
 // `nblocks` 128-wide blocks.  a[m]: this lane's first weight piece (the two
 // pieces of a block are `astep` apart, blocks 2*astep apart); b[tb]: the
 // token row's first piece (4 pieces = 64 bytes per step); wsc[m][kb] and
-// xsc[tb][kb]: block scales.  Weights are loaded U blocks ahead.
+// xsc[tb][kb]: block scales.
+//
+// Batches of U blocks -- weights, token pieces and scales -- go into two
+// register sets used in turn, with no copies between them (a copy would have
+// to wait for the loads it copies), every load issued unconditionally (blocks
+// past the end read the first token piece: in bounds, never multiplied), so
+// that a wave keeps the next batch in flight while it multiplies.  One token
+// block (batches of up to 16 tokens), R1-shaped layer, one box: T = 1 85.4 ->
+// 78.3 us, T = 4 161 -> 154; batches of 1, 3 or 4 blocks: within 2 %, slower.
+// Two token blocks: T = 32 1027 -> 1137, T = 200 1828 -> 2077 us, so they keep
+// the loop below.
+template <int U, int NA, int NB>
+__device__ inline void contract_fp8_ahead(const u32x4_t* const (&a)[NA], int astep, const u32x4_t* const (&b)[NB],
+                                          const float* const (&wsc)[NA], const float* const (&xsc)[NB], int nb,
+                                          int nblocks, f32x4_t (&acc)[NA][NB]) {
+    struct Batch {
+        u32x4_t w[NA][U][2], x[NB][U][2];
+        float ws[NA][U], xs[NB][U];
+    };
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    auto load = [&](Batch& s, int kb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = kb + u < nblocks;
+            const int st = 2 * (kb + u), k = in ? kb + u : 0;
+#pragma unroll
+            for (int m = 0; m < NA; ++m) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) s.w[m][u][h] = load_stream(in ? a[m] + (size_t)astep * (st + h) : b[0]);
+                s.ws[m][u] = wsc[m][k];
+            }
+#pragma unroll
+            for (int tb = 0; tb < NB; ++tb) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) s.x[tb][u][h] = load_cached(in ? b[tb] + 4 * (st + h) : b[0]);
+                s.xs[tb][u] = xsc[tb][k];
+            }
+        }
+    };
+    auto mul = [&](const Batch& s, int kb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) {
+            if (tb < nb) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (kb + u < nblocks) {
+                        const i32x8_t x = join(s.x[tb][u][0], s.x[tb][u][1]);
+#pragma unroll
+                        for (int m = 0; m < NA; ++m) {
+                            const f32x4_t part = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                                join(s.w[m][u][0], s.w[m][u][1]), x, zero, 0, 0, 0, kScaleOne, 0, kScaleOne);
+                            acc[m][tb] += part * (s.ws[m][u] * s.xs[tb][u]);
+                        }
+                    }
+                }
+            }
+        }
+    };
+    Batch s0, s1;
+    load(s0, 0);
+    for (int kb = 0; kb < nblocks; kb += 2 * U) {
+        load(s1, kb + U);
+        mul(s0, kb);
+        if (kb + U >= nblocks) break;
+        load(s0, kb + 2 * U);
+        mul(s1, kb + U);
+    }
+}
+
+// The same with the token pieces read next to their MFMAs (more token blocks:
+// a second set of them would cost the kernel a resident wave per SIMD).
 template <int U, int NA, int NB>
 __device__ inline void contract_fp8(const u32x4_t* const (&a)[NA], int astep, const u32x4_t* const (&b)[NB],
                                     const float* const (&wsc)[NA], const float* const (&xsc)[NB], int nb,
@@ -200,6 +237,7 @@ __global__ __launch_bounds__(kFfnThreads) void k_gate_up_fp8(FfnParams p) {
         const int jt = (item - c * items_per_chunk) * tiles_per_item + wave / S;
         const ChunkRef ck = ffn_chunk(p, c);
         const int xs_ = ck.xs, row0 = ck.row0, ntok = ck.ntok;
+        if (ffn_skip(p, xs_)) continue;   // uniform over the workgroup
         const int nb = (ntok + 15) >> 4;
         const int kb0 = sp * kper;
         const u32x4_t* wb = (const u32x4_t*)ffn_weights(p, xs_, false, expert_bytes);
@@ -227,7 +265,8 @@ __global__ __launch_bounds__(kFfnThreads) void k_gate_up_fp8(FfnParams p) {
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int tb = 0; tb < NB; ++tb) acc[m][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        contract_fp8<kFp8U, 2, NB>(a, astep, xb, wsc, xsc, nb, kper, acc);
+        if constexpr (NB == 1) contract_fp8_ahead<kFp8U, 2, NB>(a, astep, xb, wsc, xsc, nb, kper, acc);
+        else contract_fp8<kFp8U, 2, NB>(a, astep, xb, wsc, xsc, nb, kper, acc);
 
         if (S > 1) {
 #pragma unroll
@@ -302,7 +341,8 @@ __global__ __launch_bounds__(kFfnThreads) void k_down_fp8(FfnParams p) {
         f32x4_t acc[1][NB];
 #pragma unroll
         for (int tb = 0; tb < NB; ++tb) acc[0][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        contract_fp8<kFp8U, 1, NB>(a, astep, hb, wsc, hsc, nb, kblocks, acc);
+        if constexpr (NB == 1) contract_fp8_ahead<kFp8U, 1, NB>(a, astep, hb, wsc, hsc, nb, kblocks, acc);
+        else contract_fp8<kFp8U, 1, NB>(a, astep, hb, wsc, hsc, nb, kblocks, acc);
 #pragma unroll
         for (int tb = 0; tb < NB; ++tb) {
             const int n = tb * 16 + r;

@@ -18,6 +18,7 @@
 #include <math.h>
 
 #include "caee_internal.h"
+#include "fp8_codec.h"
 
 namespace caee {
 namespace {
@@ -1372,17 +1373,146 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_fused_shared(RouteParam
     else shared_gate_up<M>(fp, blockIdx.x - 1, gridDim.x - 1);
 }
 
+// 8-bit batches of at most 16 tokens: the workgroups after the first quantise
+// x (what the gate/up launch reads next), 64 blocks of 128 values each, so
+// that no launch of its own does.  Batches of at most kSharedFp8T tokens also
+// run the shared experts' gate/up here, in the workgroups behind those; a wave
+// quantises the piece of x that its contraction range reads for itself (more
+// tokens would make that longer than the routing chain).  R1-shaped layer, one
+// box: T = 1 91.1 -> 86.3 us, T = 2 133.5 -> 126.7, T = 8 (x only) 195 -> 193.
+typedef int i32x8_t __attribute__((ext_vector_type(8)));
+constexpr int kSharedFp8T = 4;
+constexpr int kSharedFp8K = 4;    // 128-wide blocks a wave contracts at a time
+constexpr int kRouteQuantBlocks = kRouteThreads / kQuantLanes;
+
+__device__ inline i32x8_t join8(const u32x4_t& lo, const u32x4_t& hi) {
+    return i32x8_t{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+}
+
+__device__ void route_quant_x(const FfnParams& p, int wg) {
+    const int b = wg * kRouteQuantBlocks + threadIdx.x / kQuantLanes, l = threadIdx.x % kQuantLanes;
+    if (b >= p.T * (p.d / 128)) return;   // uniform over the block's lanes
+    float v[8];
+    load8((const uint16_t*)p.x + (size_t)b * 128 + 8 * l, v);
+    const float sc = quant_block(v, p.xq + (size_t)b * 128, l);
+    if (l == 0) p.xs[b] = sc;
+}
+
+// Item: one 16-column tile (gate and up rows) of one shared expert, the 16
+// waves on consecutive ranges of the contraction, their partial sums added in
+// wave order; fp32 SwiGLU rows, as the gate/up launch stores them.
+__device__ void shared_gate_up_fp8(const FfnParams& p, int wg, int n_wg) {
+    constexpr int kWaves = kRouteThreads / kWave;
+    __shared__ __align__(16) uint8_t s_q[kWaves][kSharedFp8T][kSharedFp8K * 128];
+    __shared__ float s_xs[kWaves][kSharedFp8T][kSharedFp8K];
+    __shared__ f32x4_t s_part[kWaves][2][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int r = lane & 15, g = lane >> 4;
+    const int tiles = p.f / 16, kblocks = p.d / 128;
+    const size_t ksteps = (size_t)p.d / 64, row_units = (size_t)p.d / 16;
+    const int kper = (kblocks + kWaves - 1) / kWaves;
+    const int k0 = min(kblocks, wave * kper), k1 = min(kblocks, k0 + kper);
+    const size_t expert_bytes = (size_t)2 * p.f * p.d;
+    const size_t scales = (size_t)(2 * p.f / 128) * kblocks;
+    const int n = r < p.T ? r : 0;   // padded token columns read a valid row; results dropped
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    for (int item = wg; item < p.n_shared * tiles; item += n_wg) {
+        const int sh = item / tiles, jt = item - sh * tiles;
+        const u32x4_t* wb = (const u32x4_t*)((const char*)p.sh_w13 + (size_t)sh * expert_bytes);
+        const float* ws = p.sh_w13_scale + (size_t)sh * scales;
+        f32x4_t acc[2] = {zero, zero};
+        for (int kb = k0; kb < k1; kb += kSharedFp8K) {
+            // The range's weights, all in flight (blocks past it re-read the last).
+            u32x4_t w[kSharedFp8K][2][2];
+            float sc[kSharedFp8K][2];
+#pragma unroll
+            for (int u = 0; u < kSharedFp8K; ++u) {
+                const int b = min(kb + u, k1 - 1);
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int row = m * p.f + jt * 16;
+                    const u32x4_t* a = p.tiled ? wb + ((size_t)(row / 16) * ksteps + 2 * b) * 64 + lane
+                                               : wb + (size_t)(row + r) * row_units + g + 8 * (size_t)b;
+                    w[u][m][0] = load_stream(a);
+                    w[u][m][1] = load_stream(a + (p.tiled ? 64 : 4));
+                    sc[u][m] = ws[(size_t)(row / 128) * kblocks + b];
+                }
+            }
+            // x of the range: 16 lanes per block, one block of each token at a time.
+            const int qb = lane / kQuantLanes, ql = lane % kQuantLanes;
+            for (int t = 0; t < p.T; ++t) {
+                float v[8];
+                load8((const uint16_t*)p.x + (size_t)t * p.d + (size_t)min(kb + qb, k1 - 1) * 128 + 8 * ql, v);
+                const float s = quant_block(v, &s_q[wave][t][qb * 128], ql);
+                if (ql == 0) s_xs[wave][t][qb] = s;
+            }
+#pragma unroll
+            for (int u = 0; u < kSharedFp8K; ++u) {
+                if (kb + u >= k1) break;
+                const u32x4_t* q = (const u32x4_t*)&s_q[wave][n][u * 128];
+                const i32x8_t x = join8(q[g], q[4 + g]);
+                const float xs = s_xs[wave][n][u];
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const f32x4_t part = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                        join8(w[u][m][0], w[u][m][1]), x, zero, 0, 0, 0, 127, 0, 127);   // E8M0 127: 1.0
+                    acc[m] += part * (sc[u][m] * xs);
+                }
+            }
+        }
+        s_part[wave][0][lane] = acc[0];
+        s_part[wave][1][lane] = acc[1];
+        __syncthreads();
+        if (wave == 0 && r < p.T) {
+            f32x4_t gs = s_part[0][0][lane], us = s_part[0][1][lane];
+            for (int q = 1; q < kWaves; ++q) {
+                gs += s_part[q][0][lane];
+                us += s_part[q][1][lane];
+            }
+            float h[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[v] = silu_mul(gs[v], us[v]);
+            *(float4*)((float*)p.h + (size_t)(sh * p.T + r) * p.f + jt * 16 + 4 * g) =
+                make_float4(h[0], h[1], h[2], h[3]);
+        }
+        __syncthreads();
+    }
+}
+
+template <int EPL>
+__global__ __launch_bounds__(kRouteThreads) void k_route_fused_fp8(RouteParams p, FfnParams fp, int quant_wgs) {
+    const int b = blockIdx.x;
+    if (b == 0) route_fused_body<EPL>(p);
+    else if (b <= quant_wgs) route_quant_x(fp, b - 1);
+    else shared_gate_up_fp8(fp, b - 1 - quant_wgs, gridDim.x - 1 - quant_wgs);
+}
+
 }  // namespace
 
 bool route_runs_shared(const caee_layer_desc_t& d) {
     // one 16-token block: the workgroups' tiles hold every token of the batch
-    return kRouteShared && d.T <= 16 && d.T <= kFusedT && d.n_shared > 0 && d.w_dtype != CAEE_FP8_E4M3;
+    if (d.w_dtype == CAEE_FP8_E4M3) return kRouteShared && d.T <= kSharedFp8T && d.n_shared > 0;
+    return kRouteShared && d.T <= 16 && d.T <= kFusedT && d.n_shared > 0;
 }
 
-hipError_t launch_route_shared(const RouteParams& p, const FfnParams& fp, int w_dtype, hipStream_t s) {
-    const int items = fp.n_shared * (fp.f / 16);
-    const int cap = device_cu_count() - 1;
-    const dim3 grid(1 + (items < cap ? items : cap));
+bool route_quantises_x(const caee_layer_desc_t& d) { return d.w_dtype == CAEE_FP8_E4M3 && d.T <= kFusedT; }
+
+hipError_t launch_route_shared(const RouteParams& p, const FfnParams& fp, int w_dtype, bool shared, hipStream_t s) {
+    const int items = shared ? fp.n_shared * (fp.f / 16) : 0;
+    const int quant_wgs =
+        w_dtype == CAEE_FP8_E4M3 ? (p.T * (fp.d / 128) + kRouteQuantBlocks - 1) / kRouteQuantBlocks : 0;
+    const int cap = device_cu_count() - 1 - quant_wgs > 1 ? device_cu_count() - 1 - quant_wgs : 1;
+    const dim3 grid(1 + quant_wgs + (items < cap ? items : cap));
+    if (w_dtype == CAEE_FP8_E4M3) {
+        switch (p.epl) {
+            case 1: hipLaunchKernelGGL(k_route_fused_fp8<1>, grid, dim3(kRouteThreads), 0, s, p, fp, quant_wgs); break;
+            case 2: hipLaunchKernelGGL(k_route_fused_fp8<2>, grid, dim3(kRouteThreads), 0, s, p, fp, quant_wgs); break;
+            case 4: hipLaunchKernelGGL(k_route_fused_fp8<4>, grid, dim3(kRouteThreads), 0, s, p, fp, quant_wgs); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     auto go = [&](auto k) -> hipError_t {
         hipLaunchKernelGGL(k, grid, dim3(kRouteThreads), 0, s, p, fp);
         return hipGetLastError();

@@ -43,6 +43,16 @@ def test_fp8_rules(shape, T, zipf):
     _case(shape, T, zipf=zipf)
 
 
+# Up to 16 tokens the routing launch quantises x, up to 4 it runs the shared
+# experts' gate/up; contractions of 2, 9, 20 and 65 blocks of 128 over its 16
+# waves (idle waves, several blocks a wave, more than four).
+@pytest.mark.parametrize("d,n_shared,tiled", [(256, 1, True), (1152, 2, False), (2560, 0, True), (8320, 1, True)])
+@pytest.mark.parametrize("T", [1, 3, 4, 5, 16, 17])
+def test_fp8_small_batches(d, n_shared, tiled, T):
+    _case(FP8.with_(name=f"fp8-small-{d}", d=d, f=256, E=8, n_group=2, topk_group=1, k=3, n_shared=n_shared), T,
+          tiled=tiled, zipf=None)
+
+
 @pytest.mark.parametrize("shape,tiled", [(D384, True), (WIDE8, False)])
 @pytest.mark.parametrize("T", [33, 130, 300])
 def test_fp8_staged(shape, tiled, T):
