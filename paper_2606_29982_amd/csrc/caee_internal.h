@@ -35,7 +35,7 @@ constexpr int kMaxTokenBlocks = CAEE_MAX_TOKEN_BLOCKS;
 #endif
 constexpr int kPrefillT = CAEE_PREFILL_T;
 // 8-bit batches above this many tokens run their big chunks (as wide as its
-// token tile: 256 rows) with the prefill kernel of ffn_prefill8.hip, when the
+// token tile: 256 rows) with the prefill kernel of ffn_prefill8.h, when the
 // weights are tiled and the sizes fit.  Up to 32 tokens there are no big
 // chunks; from 33 on one such item (256 weight rows, the whole contraction)
 // takes about 90 us where the LDS-staged 64-row kernels took 500 us for a
