@@ -340,8 +340,9 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
     // Uploads the tables if dev_tab does not hold them already, from host
     // buffer 0 before routing or 1 after it.  The copy from buffer 0 of the
     // call before is done (its host waited for its routing, which follows
-    // that copy), and so is the one from buffer 1 once this call's routing
-    // is (`s` is behind ev_done).
+    // that copy, or returned an error and waited for everything: failed()),
+    // and so is the one from buffer 1 once this call's routing is (`s` is
+    // behind ev_done).
     auto upload = [&](int buf) -> caee_status_t {
         if (h->tab_valid && h->tab == h->tab_now) return CAEE_OK;
         char* from = h->host_tab + buf * h->tab_bytes;
@@ -352,7 +353,20 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
         h->tab_valid = true;
         return CAEE_OK;
     };
-    CAEE_TRY(upload(0));
+    // A call that ends in an error leaves nothing in flight: what it enqueued
+    // reads the caller's arrays, the slots, and host buffers that the next
+    // call rewrites.  What dev_tab holds then counts as unknown.
+    auto failed = [&](caee_status_t st) {
+        h->tab_valid = false;
+        if (hipEventRecord(h->ev_done, s) == hipSuccess) {
+            h->have_done = true;
+            if (hipEventSynchronize(h->ev_done) == hipSuccess) return st;
+        }
+        (void)hipStreamSynchronize(s);
+        return st;
+    };
+    caee_status_t st = upload(0);
+    if (st != CAEE_OK) return failed(st);
     RouteParams rp = make_route_params(desc, logits, bias, (const float*)h->dev_tab, nullptr, wsb, L);
     rp.chunk_small = call_chunk_small(d, h->layout == CAEE_LAYOUT_TILED);
     rp.chunk_big = call_chunk_big(d, h->layout == CAEE_LAYOUT_TILED);
@@ -366,25 +380,20 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
     fp.pass_of = (const int32_t*)(h->dev_tab + h->off_pass);
     fp.pass_id = 0;
     FfnCall fc;
-    CAEE_TRY(ffn_begin(desc, fp, L, s, &fc));
-    // A return below leaves work behind that reads the tables and slots: the
-    // next call waits for it.
-    auto joined = [&](caee_status_t st) {
-        if (hipEventRecord(h->ev_done, s) == hipSuccess) h->have_done = true;
-        return st;
-    };
+    st = ffn_begin(desc, fp, L, s, &fc);
+    if (st != CAEE_OK) return failed(st);
     fc.shared_done = route_runs_shared(d);   // as caee_moe_layer, so both give the same bits
-    caee_status_t st = run_route_layer(desc, rp, out, wsb, L, s, fc.shared_done ? &fp : nullptr);
-    if (st != CAEE_OK) return joined(st);
+    st = run_route_layer(desc, rp, out, wsb, L, s, fc.shared_done ? &fp : nullptr);
+    if (st != CAEE_OK) return failed(st);
     hipError_t he = hipEventRecord(h->ev_route, s);
-    if (he != hipSuccess) return joined(hip_fail(he, "hipEventRecord"));
+    if (he != hipSuccess) return failed(hip_fail(he, "hipEventRecord"));
     // The FFN of the resident and shared experts follows routing without
     // waiting for the host.
     st = ffn_routed(desc, fp, L, &fc, false);
-    if (st != CAEE_OK) return joined(st);
+    if (st != CAEE_OK) return failed(st);
     // 2. A_trans, once routing is done.
     he = hipEventSynchronize(h->ev_route);
-    if (he != hipSuccess) return joined(hip_fail(he, "waiting for routing"));
+    if (he != hipSuccess) return failed(hip_fail(he, "waiting for routing"));
 
     // 3. plan.
     std::vector<int32_t> fetch(E), fetch_slot(E);
@@ -392,7 +401,7 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
     const int64_t call = h->call;
     st = lru_plan(E, h->n_cache, h->n_stage, h->slot_of.data(), h->slot_expert.data(), h->slot_used.data(), call,
                   h->host_trans, fetch.data(), fetch_slot.data(), counts);
-    if (st != CAEE_OK) return joined(st);
+    if (st != CAEE_OK) return failed(st);
     const int misses = counts[1], staged = counts[2];
     const int batch = staged > 0 ? std::min(h->fetch_batch, h->n_stage) : h->fetch_batch;
     const int n_batches = (misses + batch - 1) / batch;
@@ -404,7 +413,8 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
             h->slot_expert[sl] = -1;
             h->slot_used[sl] = -1;
         }
-        return joined(st_);
+        (void)hipStreamSynchronize(cs);   // copies into slots that are now free
+        return failed(st_);
     };
 
     // The misses' addresses and passes (the slots of experts they replace

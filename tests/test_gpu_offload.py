@@ -62,6 +62,53 @@ def test_tiny_offload_capacity_error(tiny_w):
         h.close()
 
 
+# Calls after a capacity error, and calls on different streams, which both
+# depend on what the handle remembers of its tables and of its last call: a
+# batch of many tokens that activates every expert does not fit six slots,
+# one-token calls (4 experts) do.
+def test_tiny_offload_calls_after_capacity_error_on_two_streams(tiny_w):
+    _, Wd = tiny_w
+    Wl = dict(Wd, layout=caee.LAYOUT_ROWMAJOR)
+    big_T = 16384
+    big = make_call_sequence(TINY_F32.with_(name="tiny-many", T=big_T), seed=9, n_calls=1)[0]
+    ones = make_call_sequence(TINY_F32.with_(name="tiny-one", T=1), seed=8, n_calls=4, zipf_logit_s=1.2)
+    layer = caee.Layer.from_shape(TINY_F32, T=big_T, tau=0.0, n_bins=1)
+    one = caee.Layer.from_shape(TINY_F32, T=1, tau=0.0, n_bins=1)
+    host = caee.pin_host_weights(Wl)
+    s13, s2 = caee.alloc_slots(layer, 6, DEV)
+    miss_cost = 3.0
+    h = caee.Offload(layer, host["w13"], host["w2"], s13, s2, Wd["sh_w13"], Wd["sh_w2"], 6, 0, miss_cost, 2, 0)
+    try:
+        ws, ws1, ws2 = caee.alloc_workspace(layer, DEV), caee.alloc_workspace(one, DEV), caee.alloc_workspace(one, DEV)
+        bx, blogits = to_dev(big.x, DEV), to_dev(big.logits, DEV)
+        by = torch.full((big_T, TINY_F32.d), 7.0, device=DEV)
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        torch.cuda.synchronize()
+        for i, inp in enumerate(ones):
+            print(f"offload call {i}: T=1 after a refused T={big_T}, stream {i % 2}", flush=True)
+            before = h.residency()
+            with torch.cuda.stream(streams[i % 2]):
+                with pytest.raises(caee.CaeeError) as ei:
+                    h(layer, bx, blogits, None, by, ws)
+                idle = torch.cuda.current_stream().query()
+            assert ei.value.status == caee.CAEE_ERR_CAPACITY
+            assert idle, "work of the refused call is still in flight"
+            assert np.array_equal(h.residency(), before)
+            cost = np.where(before >= 0, 0.0, miss_cost).astype(np.float32)
+            x, logits = to_dev(inp.x, DEV), to_dev(inp.logits, DEV)
+            y, y2 = (torch.full((1, TINY_F32.d), 5.0, device=DEV) for _ in range(2))
+            caee.moe_layer(one, x, logits, None, to_dev(cost, DEV), None, Wl, y2, ws2)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(streams[1 - i % 2]):
+                h(one, x, logits, None, y, ws1)
+            torch.cuda.synchronize()
+            assert torch.equal(y, y2), "offloaded layer differs from caee_moe_layer"
+        assert torch.all(by == 7.0)
+        assert h.stats()["calls"] == len(ones)
+    finally:
+        h.close()
+
+
 def test_tiny_offload_reset_and_rejects(tiny_w):
     _, Wd = tiny_w
     calls = make_call_sequence(TINY_F32, seed=3, n_calls=2)
