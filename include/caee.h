@@ -349,7 +349,8 @@ void caee_offload_destroy(caee_offload_t* handle);
  * than the free cache slots can take and n_stage is 0.  Blocks the host
  * until the routing step has run; after a CAEE_ERR_CAPACITY or CAEE_ERR_HIP,
  * until everything that the call enqueued has run (the FFN of the resident
- * experts follows routing before the plan is known). */
+ * experts follows routing before the plan is known).  A `stream` that is
+ * being captured is refused with CAEE_ERR_HIP, nothing enqueued. */
 caee_status_t caee_offload_layer(caee_offload_t* handle, const caee_layer_desc_t* desc, const void* x,
                                  const float* logits, const float* bias, void* y, const caee_route_out_t* out,
                                  void* ws, size_t ws_bytes, void* stream, void* copy_stream);

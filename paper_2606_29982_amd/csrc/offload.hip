@@ -315,6 +315,12 @@ caee_status_t caee_offload_layer(caee_offload_t* h, const caee_layer_desc_t* des
     hipStream_t cs = reinterpret_cast<hipStream_t>(copy_stream);
     char* wsb = (char*)ws;
     const int E = d.E;
+    // The plan needs A_trans on the host, which a capture never computes; and
+    // what a capture records has not run when the call returns, so the table
+    // copy must not be taken for done, nor ev_done be recorded there.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return fail(CAEE_ERR_HIP, "stream is being captured: an offloaded call waits for its routing on the host");
 
     // Tables and slots are rewritten below; the previous call must be done with them.
     if (h->have_done) HIP_TRY(hipStreamWaitEvent(s, h->ev_done, 0), "hipStreamWaitEvent");

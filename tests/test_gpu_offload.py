@@ -109,6 +109,40 @@ def test_tiny_offload_calls_after_capacity_error_on_two_streams(tiny_w):
         h.close()
 
 
+# A call under graph capture is refused and leaves the handle as it was: the
+# next call uploads its tables (the first one has never done so) and is right.
+def test_tiny_offload_refused_under_capture(tiny_w):
+    _, Wd = tiny_w
+    Wl = dict(Wd, layout=caee.LAYOUT_ROWMAJOR)
+    layer = caee.Layer.from_shape(TINY_F32, T=16, tau=0.0, n_bins=1)
+    host = caee.pin_host_weights(Wl)
+    s13, s2 = caee.alloc_slots(layer, 16, DEV)
+    h = caee.Offload(layer, host["w13"], host["w2"], s13, s2, Wd["sh_w13"], Wd["sh_w2"], 16, 0, 3.0, 2, 0)
+    try:
+        ws, ws2 = caee.alloc_workspace(layer, DEV), caee.alloc_workspace(layer, DEV)
+        y, y2 = (torch.full((16, TINY_F32.d), 7.0, device=DEV) for _ in range(2))
+        copies = torch.cuda.Stream()
+        for i, inp in enumerate(make_call_sequence(TINY_F32, seed=7, n_calls=3)):
+            print(f"offload call {i} after one under capture", flush=True)
+            x, logits = to_dev(inp.x, DEV), to_dev(inp.logits, DEV)
+            cost = np.where(h.residency() >= 0, 0.0, 3.0).astype(np.float32)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                x.add_(0.0)
+                with pytest.raises(caee.CaeeError) as ei:
+                    h(layer, x, logits, None, y, ws, copy_stream=copies)
+            assert ei.value.status == caee.CAEE_ERR_HIP
+            assert h.stats()["calls"] == i
+            g.replay()
+            h(layer, x, logits, None, y, ws, copy_stream=copies)
+            caee.moe_layer(layer, x, logits, None, to_dev(cost, DEV), None, Wl, y2, ws2)
+            torch.cuda.synchronize()
+            assert torch.equal(y, y2), "offloaded layer differs from caee_moe_layer"
+    finally:
+        h.close()
+
+
 def test_tiny_offload_reset_and_rejects(tiny_w):
     _, Wd = tiny_w
     calls = make_call_sequence(TINY_F32, seed=3, n_calls=2)
