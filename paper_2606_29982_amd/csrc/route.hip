@@ -1398,6 +1398,14 @@ __device__ void route_quant_x(const FfnParams& p, int wg) {
     if (l == 0) p.xs[b] = sc;
 }
 
+// What the lanes of a wave have written to LDS is read by its other lanes
+// after this, and what they have read may be overwritten.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Item: one 16-column tile (gate and up rows) of one shared expert, the 16
 // waves on consecutive ranges of the contraction, their partial sums added in
 // wave order; fp32 SwiGLU rows, as the gate/up launch stores them.
@@ -1439,7 +1447,10 @@ __device__ void shared_gate_up_fp8(const FfnParams& p, int wg, int n_wg) {
                     sc[u][m] = ws[(size_t)(row / 128) * kblocks + b];
                 }
             }
-            // x of the range: 16 lanes per block, one block of each token at a time.
+            // x of the range: 16 lanes per block, one block of each token at a
+            // time.  The codes and scales go to other lanes of the wave
+            // through LDS: ordered by the fences below (the wave's LDS
+            // operations run in order; the fences keep the compiler to it).
             const int qb = lane / kQuantLanes, ql = lane % kQuantLanes;
             for (int t = 0; t < p.T; ++t) {
                 float v[8];
@@ -1447,6 +1458,7 @@ __device__ void shared_gate_up_fp8(const FfnParams& p, int wg, int n_wg) {
                 const float s = quant_block(v, &s_q[wave][t][qb * 128], ql);
                 if (ql == 0) s_xs[wave][t][qb] = s;
             }
+            wave_lds_sync();
 #pragma unroll
             for (int u = 0; u < kSharedFp8K; ++u) {
                 if (kb + u >= k1) break;
@@ -1460,6 +1472,7 @@ __device__ void shared_gate_up_fp8(const FfnParams& p, int wg, int n_wg) {
                     acc[m] += part * (sc[u][m] * xs);
                 }
             }
+            wave_lds_sync();   // before the next range's codes replace these
         }
         s_part[wave][0][lane] = acc[0];
         s_part[wave][1][lane] = acc[1];
