@@ -504,13 +504,34 @@ __global__ __launch_bounds__(kTokThreads) void k_route_tokens(RouteParams p) {
 // A popular expert of a 4096-token batch has thousands of hits, so that chain
 // is what is left: 4096 skewed tokens, SUM: 30 us (one wave per
 // expert reading block after block, readlane per hit: 258 us).
-#ifndef CAEE_PAIR_STATS
-#define CAEE_PAIR_STATS 32768
-#endif
 constexpr int kStatWaves = 4, kStatBlk = 4;
 constexpr int kStatTile = 4096;                       // tokens per tile
 constexpr int kStatWaveTok = kStatTile / kStatWaves;  // a wave's part of it
 constexpr int kStatAct = 1, kStatMust = 2;            // flags left in p.trans
+
+// Whether a batch above kFusedT tokens takes its statistics from this kernel.
+// SUM: always (nothing else computes the sums).  MAX and CIR: k_prune gathers
+// them itself from the pairs, in time by the pairs; this kernel takes time by
+// the tokens, in whole tiles, whatever k is.  So it pays for long lists from
+// 33000 pairs on, for k = 8 where the tokens fill their tiles or are many, and
+// never for k <= 4 or rows that are not 16-byte aligned.  caee_route_prune, MAX, N(0,1)
+// logits, pairs / this kernel:
+//   k = 16, E = 256: T = 1500 29.9 / 32.3 us, 2000 equal, 2500 38.2 / 35.9,
+//                    4096 50.7 / 40.8, 65536 593 / 392;
+//   k = 12, E = 256: T = 2000 27.8 / 29.7, 2800 33.7 / 32.4, 8192 70.7 / 57.1;
+//   k = 8, E = 256:  T = 2048 23.2 / 27.3, 4096 33.4 / 31.8, 6000 43.5 / 44.8,
+//                    8192 53.9 / 50.1, 9001 58.6 / 59.5, 22000 124 / 116;
+//         E = 64:    T = 9001 46.4 / 52.1, 12288 59.2 / 56.7, 32768 141 / 135;
+//   k = 6, E = 64:   T = 6000 29.3 / 52.3, 65536 215 / 364;
+//   k = 4, E = 256:  T = 8192 36.7 / 41.9;  k = 2, E = 64: T = 65536 110 / 250.
+inline bool takes_pair_stats(const RouteParams& p) {
+    if (p.rule == CAEE_IMPORTANCE_SUM) return true;
+    if (p.k % 4 != 0 || p.k < 8) return false;
+    if (p.k > 8) return (long long)p.T * p.k >= 33000;
+    const int last = p.T % kStatTile;   // k = 8: four tiles, or the last one at least 15/16 full
+    return p.T >= 4 * kStatTile || (p.T >= kStatTile && (last == 0 || last >= kStatTile / 16 * 15));
+}
+
 __global__ __launch_bounds__(kStatWaves * kWave) void k_expert_stats(RouteParams p) {
     __shared__ __align__(16) double s_g[kStatWaves][kStatWaveTok + 16];   // read up to 16 past the end
     __shared__ int s_n[kStatWaves];
@@ -1551,7 +1572,7 @@ hipError_t launch_route(const RouteParams& p, hipStream_t s) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         RouteParams q = p;
-        q.pair_stats = p.rule == CAEE_IMPORTANCE_SUM || (long long)p.T * p.k >= CAEE_PAIR_STATS;
+        q.pair_stats = takes_pair_stats(p);
         if (q.pair_stats) {
             hipLaunchKernelGGL(k_expert_stats, dim3(p.E), dim3(kStatWaves * kWave), 0, s, p);
             e = hipGetLastError();
