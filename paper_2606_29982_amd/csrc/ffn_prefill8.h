@@ -192,8 +192,15 @@ __global__ __launch_bounds__(kP8Threads) void k_prefill8(FfnParams p) {
     const size_t ksteps = (size_t)K / 64;          // 64-byte steps of a weight row (tiled layout)
     const size_t row_units = (size_t)K / 16;       // 16-byte pieces of a token row
     const int groups = kGateUp ? p.f / 128 : p.d / 256;
-    // Groups per item (uniform): a run of up to G groups of one chunk.
-    const int G = kblocks % 4 == 0 ? kRun : 1;
+    // Groups per item (uniform): a run of up to G groups of one chunk, shorter
+    // while such items are fewer than the CUs (a few popular experts of a
+    // decode batch: with runs of four a chunk's down groups were a handful of
+    // items of about 100 us beside idle CUs).  FFN of 8-bit calls, runs of four
+    // always / shortened: d = 1024, f = 2048, E = 16, k = 2, skewed T = 128 98 /
+    // 59 us; R1-shaped, skewed T = 128 538 / 530; d = 4096, f = 512, E = 32,
+    // k = 2, skewed T = 250 113 / 88, evenly used 73.5 / 75.8.
+    int G = kblocks % 4 == 0 ? kRun : 1;
+    while (G > 1 && ffn_list_size(p) * ((groups + G - 1) / G) < (int)gridDim.x / CAEE_P8_GRID_PER_CU) G >>= 1;
     const int runs = (groups + G - 1) / G;
     const int total = ffn_list_size(p) * runs;
     // Weight tiles from one group to the next (gate/up: 8 feature tiles of

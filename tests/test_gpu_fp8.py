@@ -48,10 +48,10 @@ def test_tiny_fp8_batches(T):
 
 
 # d = f = 1024: both contractions are multiples of four 128-deep blocks, so
-# the prefill kernel runs several weight groups of a chunk back to back in
-# one item (8 gate/up groups of 128 features, 4 down groups of 256 rows).
-# d = 1280: five down groups, so a chunk's last run of groups is shorter
-# (and gate/up's ten-block contraction runs one group per item).
+# down items may run several weight groups of a chunk back to back (8 gate/up
+# groups of 128 features, 4 down groups of 256 rows).  d = 1280: five down
+# groups.  These batches have too few chunks for that (test_fp8_down_runs below
+# has enough): their items are single groups.
 # 400 tokens: routed chunks of about 100 rows (7 token tiles) and the shared
 # expert's 400 rows in two chunks of 200 (13 tiles); every output compared.
 MID_FP8 = TINY_FP8.with_(name="mid-fp8", d=1024, f=1024)
@@ -62,6 +62,26 @@ MID_FP8_5 = TINY_FP8.with_(name="mid-fp8-5", d=1280, f=1024)
 def test_mid_fp8_prefill(seed, shape):
     rel = _tiny(seed, 0.1, 4, T=400, tiled=True, shape=shape)
     print(f"  {shape.name}: max|err|/max|ref| = {rel:.3e}")
+
+
+# Down items of four groups (129 chunks of 5 groups, so a chunk's last run is a
+# single group) and of two (129 chunks of 4 groups), which an MI355X's 256 CUs
+# take at 200 tokens over 128 experts and the shared one; 60 tokens leave the
+# experts without eight rows each in the small list and the runs at one group.
+@pytest.mark.parametrize("d,T", [(1280, 200), (1024, 200), (1280, 60)])
+def test_fp8_down_runs(d, T):
+    shape = TINY_FP8.with_(name=f"runs-fp8-{d}", d=d, f=512, E=128, n_group=4, topk_group=4, k=8)
+    W = make_expert_weights_torch(shape, seed=2, device=DEV)
+    inp = make_routing_inputs(shape, seed=2, T=T, n_bins=4)
+    print(f"fp8 down runs d={d} T={T}", flush=True)
+    got = gpu_layer(shape, inp, 0.0, 4, caee.pack_weights(W, "fp8"), DEV)
+    tokens = list(range(0, T, 9))
+    get, get_sh = getters_dev(W, "fp8")
+    ref = oracle_layer(shape, inp, 0.0, 4, get, get_sh, tokens=tokens)
+    check_route(got, ref, shape.E)
+    if T == 200:
+        assert ref["stats"]["n_act"] == 128
+    check_y(got["y"][tokens], ref["y"], 6e-2)
 
 
 def test_tiny_fp8_sum_rule():
