@@ -297,6 +297,30 @@ caee_status_t down_list(const caee_layer_desc_t* d, FfnParams p, int list, int n
     return timed_launch(CAEE_KERNEL_DOWN, s, "down", [&] { return launch_down(p, d->w_dtype, nb, max_chunks, s); });
 }
 
+// Which of the two lists stays on the main stream: the other one starts some
+// 10 us later.  Without shared experts a batch may have no big chunk at all, and
+// the small ones are the call; with them there is one of T rows at least.  An
+// 8-bit big item takes a whole CU for about 90 us and, behind the small ones,
+// waits for those to drain; fp32 ones are longer still; bf16 ones come first
+// where the small list is over sooner than they are.  Beyond that the big ones
+// come first where the experts have rows enough that most of the work is
+// theirs, or that some are popular beside a small list of a millisecond.
+// FFN, small / big list on the main stream:
+//   none shared: 8-bit d = 2048, f = 768, E = 128, k = 8, T = 64 136 / 151 us;
+//     bf16 d = 4096, f = 512, E = 32, k = 2, T = 64 94 / 106, skewed 94 / 80;
+//     fp32 d = 1024, f = 2048, E = 16, k = 2, T = 64 (8 rows a routed expert)
+//     112 / 123, skewed 227 / 213, T = 250 (31) 254 / 229;
+//   shared: R1-shaped, 8-bit T = 200 1854 / 1801, bf16 skewed T = 96 (3 rows)
+//     834 / 862, T = 128 (4) 942 / 962, T = 250 (7.8) 1252 / 1198;
+//     bf16 d = 4096, f = 1536, E = 128, k = 8, skewed T = 160 (10) 436 / 455,
+//     d = 2048, f = 256, E = 64, k = 6, T = 64 81.5 / 77, skewed 73 / 63.
+bool big_list_first(const caee_layer_desc_t& d) {
+    const long long pairs = (long long)d.T * d.k;
+    const long long weights = (pairs < d.E ? pairs : d.E) * 3 * d.d * d.f * elem_bytes(d.w_dtype);
+    if (d.n_shared > 0 && (d.w_dtype != CAEE_BF16 || weights < (512LL << 20))) return true;
+    return pairs >= 12LL * d.E || (d.w_dtype != CAEE_FP8_E4M3 && pairs >= 7LL * d.E && weights >= (8LL << 30));
+}
+
 }  // namespace
 
 caee_status_t ffn_begin(const caee_layer_desc_t* d, const FfnParams& p, const WsLayout& L, hipStream_t s,
@@ -317,31 +341,30 @@ caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const W
     const bool all_big = call_chunk_small(*d, p.tiled) == 0;   // then the small list is empty
     hipStream_t s = call->main;
     // The 8-bit prefill kernel reads its rows' block scales transposed and in
-    // permuted row order: gathered here for x (before the fork, so that the
-    // big chunks' gate/up is the first of the two to find the CUs free),
-    // written so by its own gate/up for H.
+    // permuted row order: gathered here for x, written so by its own gate/up
+    // for H.
     const bool gemm8 = nb_big && d->w_dtype == CAEE_FP8_E4M3 && gemm_fp8_applies(*d, p.tiled);
-    if (gemm8) {
+    auto gather = [&](hipStream_t st) -> caee_status_t {
         FfnParams pb = p;
         pb.list = 1;
-        CAEE_TRY(timed_launch(CAEE_KERNEL_QUANT, s, "gather x scales",
-                              [&] { return launch_gather_xs(pb, L.grid_chunks, s); }));
-    }
-    // The small chunks (many, bandwidth-bound) run on a side stream next to
-    // the big ones (few, long work items): disjoint rows.  The fork comes
-    // after routing, which built their lists, and the side stream starts some
-    // 6 us later, so the big items, each of which needs a whole CU, are placed
-    // first; behind the small ones they waited for those to drain (R1-shaped
-    // layer: 8-bit T = 200 1939 -> 1886 us, skewed 727 -> 704; bf16 skewed
-    // T = 300 1543 -> 1469, others within 1 %).
-    hipStream_t s_small = s;
-    if (nb_big && !all_big && two_streams && kBigConcurrent) {
+        return timed_launch(CAEE_KERNEL_QUANT, st, "gather x scales",
+                            [&] { return launch_gather_xs(pb, L.grid_chunks, st); });
+    };
+    // The two lists run beside each other (disjoint rows), one on a side
+    // stream forked after routing, which built them (see big_list_first).
+    const bool forked = nb_big && !all_big && two_streams && kBigConcurrent;
+    const bool big_first = !forked || big_list_first(*d);
+    hipStream_t s_small = s, s_big = s;
+    // On the main stream the gather comes before the fork, so that the big
+    // chunks' gate/up is the first of the two to find the CUs free.
+    if (gemm8 && big_first) CAEE_TRY(gather(s));
+    if (forked) {
         SideStream* ss = nullptr;
         CAEE_TRY(side_stream(&ss));
         call->side = ss->stream;
         call->ev_join = ss->join;
         CAEE_TRY(order(ss->fork, s, ss->stream, "fork to the side stream"));
-        s_small = call->side;
+        (big_first ? s_small : s_big) = call->side;
     }
     // Gate/up skips the shared experts when the routing launch ran them.
     FfnParams pg = p;
@@ -358,6 +381,11 @@ caee_status_t ffn_routed(const caee_layer_desc_t* d, const FfnParams& p, const W
         }
         return down_list(d, p, list, nb, L.grid_chunks, st);
     };
+    if (!big_first) {
+        CAEE_TRY(chain(0, nb_small, s));
+        if (gemm8) CAEE_TRY(gather(s_big));
+        return chain(1, nb_big, s_big);
+    }
     if (nb_big) CAEE_TRY(chain(1, nb_big, s));
     return all_big ? CAEE_OK : chain(0, nb_small, s_small);
 }
@@ -415,8 +443,8 @@ caee_status_t check_layer_args(const caee_layer_desc_t* desc, const void* x, con
     return CAEE_OK;
 }
 
-// The whole layer on validated arguments and a checked workspace; the small
-// chunks run on a second stream next to the big ones when `side` is set.
+// The whole layer on validated arguments and a checked workspace; one of the
+// two chunk lists runs on a second stream when `side` is set.
 caee_status_t moe_layer_run(const caee_layer_desc_t* desc, const void* x, const float* logits, const float* bias,
                             const float* cost, const int32_t* bin, const caee_expert_weights_t* weights, void* y,
                             const caee_route_out_t* out, char* wsb, const WsLayout& L, hipStream_t s, bool side) {

@@ -110,7 +110,7 @@ constexpr int kDownU1 = CAEE_DOWN_U1;
 #define CAEE_BIG_STAGED 1
 #endif
 constexpr bool kBigStaged = CAEE_BIG_STAGED != 0;
-// Run the small-chunk launches on a second stream, concurrently with the big ones.
+// Run one chunk list's launches on a second stream, concurrently with the other's.
 #ifndef CAEE_BIG_CONCURRENT
 #define CAEE_BIG_CONCURRENT 1
 #endif
@@ -521,9 +521,9 @@ void set_route_outputs(RouteParams& p, const caee_route_out_t* out, char* ws, co
 
 // The FFN of one layer call, in three parts:
 //   ffn_begin   (fp8) quantises x, unless the routing launch does (x_done);
-//   ffn_routed  after the permutation, runs the big chunks on the main
-//               stream and (two_streams) the small chunks on a side stream
-//               forked from it; with p.pass_of set only pass p.pass_id runs;
+//   ffn_routed  after the permutation, runs one chunk list on the main stream
+//               and (two_streams) the other on a side stream forked from it;
+//               with p.pass_of set only pass p.pass_id runs;
 //   ffn_end     joins the side stream and combines into y.
 struct FfnCall {
     hipStream_t main = nullptr, side = nullptr;   // side == main until forked

@@ -66,6 +66,18 @@ def test_bf16_rules(T, tiled):
     _case(BF16, T, tiled=tiled)
 
 
+# Which chunk list stays on the main stream: the small one without shared
+# experts, until the routed experts have 12 rows each (48 tokens here); the big
+# one with them.  Popular experts, so that both lists hold chunks; row-major and
+# d = 384 as well, whose big chunks other kernels take.
+@pytest.mark.parametrize("shape", [TINY_F32, BF16, FP8])
+@pytest.mark.parametrize("n_shared,T", [(0, 33), (0, 47), (0, 48), (2, 47)])
+@pytest.mark.parametrize("d,tiled", [(256, True), (384, True), (256, False)])
+def test_list_order(shape, n_shared, T, d, tiled):
+    _case(shape.with_(name=f"order-{shape.w_dtype}-{d}-{n_shared}", d=d, n_shared=n_shared), T, tiled=tiled,
+          tol=1e-5 if shape.w_dtype == "f32" else None)
+
+
 # Contractions whose stage counts leave 1, 2 and 3 steps after the stage loop
 # (bf16: 64-element stages; 8-bit: 128), every token-tile count, experts in one
 # chunk and in several (whose weights take the cached loads), odd tile counts

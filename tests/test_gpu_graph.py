@@ -31,7 +31,8 @@ class Buffers:
 
 
 @pytest.mark.parametrize("shape,T,tiled", [(TINY_F32, 5, False), (TINY_F32, 40, False), (TINY_BF16, 40, True),
-                                           (TINY_FP8, 600, True)])
+                                           (TINY_FP8, 600, True), (TINY_F32.with_(n_shared=0), 40, False),
+                                           (TINY_FP8.with_(E=64, n_group=8, n_shared=0), 100, True)])
 def test_graph_replays_match_eager(shape, T, tiled):
     print(f"graph {shape.name} T={T} tiled={tiled}", flush=True)
     n_bins = 4
