@@ -214,13 +214,7 @@ inline int big_token_blocks(const caee_layer_desc_t& d) {
     return nb < kMaxTokenBlocks ? nb : kMaxTokenBlocks;
 }
 
-#ifndef CAEE_ALL_BIG_FP8
-#define CAEE_ALL_BIG_FP8 8
-#endif
-#ifndef CAEE_ALL_BIG_BF16
-#define CAEE_ALL_BIG_BF16 14
-#endif
-constexpr int kAllBigRowsFp8 = CAEE_ALL_BIG_FP8, kAllBigRowsBf16 = CAEE_ALL_BIG_BF16;   // see call_chunk_small
+constexpr int kAllBigRowsFp8 = 8, kAllBigRowsFp8Large = 10, kAllBigRowsBf16 = 14;   // see call_chunk_small
 bool gemm_fp8_applies(const caee_layer_desc_t& d, bool tiled);
 bool gemm_bf16_applies(const caee_layer_desc_t& d, bool tiled);
 int gemm_fp8_blocks();         // 16-token blocks of an 8-bit big chunk
@@ -243,16 +237,21 @@ inline int call_big_blocks(const caee_layer_desc_t& d, bool tiled) {
 // token block once per weight tile from L2, the big-chunk ones once per
 // workgroup through LDS, but a big-chunk item is a workgroup wide, so with few
 // chunks the last round of items is nearly empty.  The line lies at a mean
-// number of rows per routed expert (R1-shaped layer, evenly used experts):
-//   8-bit: T = 200 (6.25 rows) 1914 us with small chunks, 1923 without;
-//          T = 400 (12.5) 2299 / 2024; T = 600 (18.8) 2810 / 2051;
-//          T = 1000 (31) 2754 / 2189; T = 2500 equal;
-//   bf16:  T = 300 (9.4) 3589 / 3688; T = 400 (12.5) 3613 / 3684; T = 500
+// number of rows per routed expert, for 8-bit layers of more than 1 GB of routed
+// weights (whose small list hides its fork and join) higher than for others:
+//   8-bit, R1-shaped, small chunks / none: T = 256 (8 rows) 1874 / 1937 us,
+//          skewed 700 / 782; T = 320 (10) 1972 / 1899, skewed 703 / 729;
+//          T = 400 (12.5) 2299 / 2024; T = 600 (18.8) 2810 / 2051; T = 2500 equal;
+//   8-bit, d = 4096, f = 1536, E = 128, k = 8, one shared: T = 128 (8) 467 / 503,
+//          T = 160 (10) 480 / 506, skewed 266 / 292; d = 2048, f = 1408, E = 64, k = 6: T = 86 (8)
+//          151 / 133, skewed 123 / 113;
+//   bf16, R1-shaped: T = 300 (9.4) 3589 / 3688; T = 400 (12.5) 3613 / 3684; T = 500
 //          (15.6) 4020 / 3767; T = 800 (25) 4643 / 4065.
 inline int call_chunk_small(const caee_layer_desc_t& d, bool tiled) {
     const int nb = big_token_blocks(d);
     const long long pairs = (long long)d.T * d.k;
-    if (nb > 0 && gemm_fp8_applies(d, tiled) && pairs >= (long long)kAllBigRowsFp8 * d.E) return 0;
+    const long long rows8 = (long long)d.E * 3 * d.d * d.f > (1LL << 30) ? kAllBigRowsFp8Large : kAllBigRowsFp8;
+    if (nb > 0 && gemm_fp8_applies(d, tiled) && pairs >= rows8 * d.E) return 0;
     if (nb > 0 && gemm_bf16_applies(d, tiled) && pairs >= (long long)kAllBigRowsBf16 * d.E) return 0;
     return 16 * small_token_blocks(d);
 }

@@ -151,6 +151,21 @@ def test_r1_fp8_decode(T, tokens, rule, tau, r1_fp8):
     print(f"  {len(toks)} tokens: max|err|/max|ref| = {rel:.3e}", flush=True)
 
 
+# The last batch of a layer of more than 1 GB whose experts of up to 32 rows are
+# small chunks (under 10 rows per expert), and the first whose chunks are all big.
+@pytest.mark.parametrize("T", [319, 320])
+def test_r1_fp8_all_big_line(T, r1_fp8):
+    W, Wt = r1_fp8
+    inp = make_routing_inputs(R1_FP8, seed=6, T=T, zipf_logit_s=1.1, n_bins=8)
+    print(f"fp8 R1 T={T}", flush=True)
+    got = gpu_layer(R1_FP8, inp, 0.0, 8, Wt, DEV)
+    tokens = [0, T // 2, T - 1]
+    get, get_sh = getters_dev(W, "fp8")
+    ref = oracle_layer(R1_FP8, inp, 0.0, 8, get, get_sh, tokens=tokens)
+    check_route(got, ref, R1_FP8.E)
+    check_y(got["y"][tokens], ref["y"], 6e-2)
+
+
 def prefill_subset(topk_ids, T, n_shared, n=256, chunk=128, seed=0):
     """A fixed subset of ``n`` tokens of a prefill batch that covers the
     edges of the FFN's work items: an expert slot with r rows is cut into
