@@ -78,13 +78,17 @@ __device__ inline u32x4_t load_cached(const u32x4_t* p) { return *(g_u32x4_t*)p;
 //
 // Batches of U blocks -- weights, token pieces and scales -- go into two
 // register sets used in turn, with no copies between them (a copy would have
-// to wait for the loads it copies), every load issued unconditionally (blocks
-// past the end read the first token piece: in bounds, never multiplied), so
-// that a wave keeps the next batch in flight while it multiplies.  One token
-// block (batches of up to 16 tokens), R1-shaped layer, one box: T = 1 85.4 ->
-// 78.3 us, T = 4 161 -> 154; batches of 1, 3 or 4 blocks: within 2 %, slower.
-// Two token blocks: T = 32 1027 -> 1137, T = 200 1828 -> 2077 us, so they keep
-// the loop below.
+// to wait for the loads it copies), so that a wave keeps the next batch in
+// flight while it multiplies.  A batch's loads are unconditional (blocks past
+// the end of the last one read the first token piece: in bounds, never
+// multiplied); where no batch follows, the multiply is a copy of its own without
+// loads, so that the count of loads behind a batch is one number on each path.
+// One token block (batches of up to 16 tokens), R1-shaped layer, one box: T = 1
+// 85.4 -> 78.3 us, T = 4 161 -> 154; batches of 1, 3 or 4 blocks: within 2 %,
+// slower; with a batch of dummy loads after the last one T = 16 645 -> 653, FFN
+// of d = 2048, f = 256, E = 64, k = 6, T = 12 (two and one batches an item) 31.6 ->
+// 33.4.  Two token blocks: T = 32 1027 -> 1137, T = 200 1828 -> 2077 us, so they
+// keep the loop below.
 template <int U, int NA, int NB>
 __device__ inline void contract_fp8_ahead(const u32x4_t* const (&a)[NA], int astep, const u32x4_t* const (&b)[NB],
                                           const float* const (&wsc)[NA], const float* const (&xsc)[NB], int nb,
@@ -134,10 +138,17 @@ __device__ inline void contract_fp8_ahead(const u32x4_t* const (&a)[NA], int ast
     };
     Batch s0, s1;
     load(s0, 0);
-    for (int kb = 0; kb < nblocks; kb += 2 * U) {
+    for (int kb = 0;; kb += 2 * U) {
+        if (kb + U >= nblocks) {
+            mul(s0, kb);
+            break;
+        }
         load(s1, kb + U);
         mul(s0, kb);
-        if (kb + U >= nblocks) break;
+        if (kb + 2 * U >= nblocks) {
+            mul(s1, kb + U);
+            break;
+        }
         load(s0, kb + 2 * U);
         mul(s1, kb + U);
     }
