@@ -346,8 +346,7 @@ __device__ inline uint64_t splitmix64(uint64_t state) {
 // Phase C for token t: K_final = (K_t ∩ A_trans) refilled from A_trans \ K_t.
 template <int EPL>
 __device__ void compensate_token(const RouteParams& p, int t, int lane, const int* orig,
-                                 const uint8_t* trans, int* fin, double* sbuf, int* n_refill,
-                                 int* n_pad) {
+                                 const uint8_t* trans, int* n_refill, int* n_pad) {
     bool in_k[EPL], tr[EPL], out_f[EPL];
     // K_t: lane r < k holds its r-th expert; the list is broadcast lane by lane.
     const int my_orig = lane < p.k ? orig[lane] : -1;
@@ -382,13 +381,11 @@ __device__ void compensate_token(const RouteParams& p, int t, int lane, const in
         const int pos = __popcll(kept_mask & ((1ull << lane) - 1ull));
         if (kept) {
             const size_t o = (size_t)t * p.k + pos;
-            fin[pos] = my_orig;
             p.topk_ids[o] = my_orig;
             p.topk_w[o] = (float)(p.rs * (my_s / total));
         }
         if (lane >= n_keep && lane < p.k) {
             const size_t o = (size_t)t * p.k + lane;
-            fin[lane] = -1;
             p.topk_ids[o] = -1;
             p.topk_w[o] = 0.0f;
         }
@@ -471,7 +468,6 @@ __device__ void compensate_token(const RouteParams& p, int t, int lane, const in
     if (lane < p.k) {
         const size_t o = (size_t)t * p.k + lane;
         const bool have = lane < m;
-        fin[lane] = have ? my_id : -1;
         p.topk_ids[o] = have ? my_id : -1;
         p.topk_w[o] = have ? (float)(p.rs * (my_s / total)) : 0.0f;
     }
@@ -1217,8 +1213,6 @@ hipError_t launch_permutation(const RouteParams& p, hipStream_t s) {
 template <int EPL>
 __global__ __launch_bounds__(kTokThreads) void k_compensate(RouteParams p) {
     __shared__ uint8_t s_trans[kMaxE];
-    __shared__ double s_sbuf[kTokWaves][kMaxK];
-    __shared__ int s_fin[kTokWaves][kMaxK];
     __shared__ int s_cnt[2];   // refilled and empty slots of the workgroup's tokens
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -1227,8 +1221,7 @@ __global__ __launch_bounds__(kTokThreads) void k_compensate(RouteParams p) {
     if (tid < 2) s_cnt[tid] = 0;
     __syncthreads();
     for (int t = blockIdx.x * kTokWaves + wave; t < p.T; t += gridDim.x * kTokWaves)
-        compensate_token<EPL>(p, t, lane, p.orig_ids + (size_t)t * p.k, s_trans, s_fin[wave], s_sbuf[wave],
-                              &s_cnt[0], &s_cnt[1]);
+        compensate_token<EPL>(p, t, lane, p.orig_ids + (size_t)t * p.k, s_trans, &s_cnt[0], &s_cnt[1]);
     // One global update per workgroup (per-token updates of the same two
     // words serialise in the L2).
     __syncthreads();
@@ -1249,8 +1242,6 @@ constexpr int kFusedWaves = kRouteThreads / kWave;
 
 template <int EPL>
 __device__ void route_fused_body(const RouteParams& p) {
-    __shared__ double s_sbuf[kFusedWaves][kMaxK];
-    __shared__ int s_ids[kFusedWaves][kMaxK];
     __shared__ PruneShared sp;
     __shared__ PermShared sq;
     __shared__ int32_t l_orig[kFusedT * kMaxK], l_top1[kFusedT], l_fin[kFusedT * kMaxK];
@@ -1311,8 +1302,7 @@ __device__ void route_fused_body(const RouteParams& p) {
         }
     } else {
         for (int t = wave; t < p.T; t += kFusedWaves)
-            compensate_token<EPL>(q, t, lane, q.orig_ids + (size_t)t * k, l_trans, s_ids[wave], s_sbuf[wave],
-                                  &s_cnt[0], &s_cnt[1]);
+            compensate_token<EPL>(q, t, lane, q.orig_ids + (size_t)t * k, l_trans, &s_cnt[0], &s_cnt[1]);
     }
     __syncthreads();
     if (tid < 2) l_counts[tid] = s_cnt[tid];   // the only workgroup: the call's totals
