@@ -227,9 +227,10 @@ __global__ __launch_bounds__(kGemmThreads, 2) void k_gemm(FfnParams p) {
             // v - 3, whose ring slot the tokens of block v + 1 then refill,
             // and multiplies block v - 2.  Steps past the last block re-read
             // it, so the waits are constants.  The remaining steps after the
-            // loop wait for all but the token loads of the two steps before:
-            // nothing multiplies the weights they re-read, so the compiler
-            // may leave those loads out.
+            // loop (three at most) wait for all but the token loads of the two
+            // steps before: nothing multiplies the weights that are re-read,
+            // so the compiler may leave those loads out of what a count would
+            // include.
             auto step = [&](int v, auto jc, auto mc, auto tc) __attribute__((always_inline)) {
                 constexpr int J = decltype(jc)::value;
                 const int u = v + 1 < nblk ? v + 1 : nblk - 1;

@@ -519,8 +519,14 @@ __global__ __launch_bounds__(kP8Threads) void k_prefill8(FfnParams p) {
             // sets it waits for the loads of step v - 3 (the tokens and
             // weights of block v - 2).
             // The steps after the loop (kTail) wait for all but the token loads
-            // of the two steps before: nothing multiplies the weights they
-            // re-read, so the compiler may leave those loads out.
+            // of the two steps before.  What the last steps re-read nothing
+            // multiplies, and the compiler leaves those loads out, so a count
+            // that takes them for outstanding would be wrong.  Earlier ones wait
+            // with it for weights of the next block too; a wait that counts the
+            // loads still multiplied (by a branch on the step), and re-reads kept
+            // alive under the loop's count, were no faster: T = 4096 gate/up 1570
+            // us, 1571, 1588, down 905, 902, 906; skewed T = 2000 gate/up 930,
+            // 931, 950.
             auto step = [&](int v, auto jc, auto mc, auto tc) __attribute__((always_inline)) {
                 constexpr int J = decltype(jc)::value;
                 constexpr bool kMult = decltype(mc)::value, kTail = decltype(tc)::value;
